@@ -480,13 +480,9 @@ void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const floa
         ldv = M.W.vt_ld;
         v_hs = uint64_t(dh) * ldv;
     }
-    // The attention kernel of several tokens (and of a single one without a cache) wants its queries scaled: whichever launch
-    // rounds them last does it, the rotary embedding or the product (a single token's product does both).
-    const float q_scale = dlk::attention_q_scale(dh);
-    const bool scaled = !(T == 1 && cache), in_post = T == 1 || d.rope_theta > 0.0f;
-    const float q_post_scale = scaled && in_post ? q_scale : 1.0f;
-    dlk::QkvPostArgs qp{qkv, L.n_qkv, T, pos0, Hq, Hkv, dh, d.rope_theta, kc, k_hs, vt, v_hs, ldv, 0, dq, dq + dkv,
-                        q_post_scale};
+    // The attention kernel of several tokens wants its queries scaled: the product does it, in front of its rounding.  (A single
+    // token without a cache goes there too: its one key has the weight 1 whatever the score.)
+    dlk::QkvPostArgs qp{qkv, L.n_qkv, T, pos0, Hq, Hkv, dh, d.rope_theta, kc, k_hs, vt, v_hs, ldv, 0, dq, dq + dkv};
     lin_work(Td, L.n_qkv, dm, &fl, &by);
     kbegin(DL_K_GEMM_QKV, fl, by);
     if (T == 1) {
@@ -497,9 +493,9 @@ void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const floa
         kend();
     } else {
         const dlk::GemmArgs g{nbuf, dm, P(L.w_qkv), dm, P(L.b_qkv), qkv, L.n_qkv, nullptr, 0, T, L.n_qkv, dm, dlk::EPI_BF16,
-                              vt + pos0, dq + dkv, ldv, q_scale, in_post ? 0 : dq};
+                              vt + pos0, dq + dkv, ldv, dlk::attention_q_scale(dh), dq};
         const bool post = d.rope_theta > 0.0f || kc;
-        const bool fused = in_post && post && dlk::gemm_qkv_post(g, qp, st);
+        const bool fused = d.rope_theta > 0.0f && dlk::gemm_qkv_post(g, qp, st);
         if (!fused) dlk::gemm(g, st);
         kend();
         if (post && !fused) {
@@ -546,7 +542,7 @@ void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const floa
                2.0 * (2.0 * double(dq) * dm + 2.0 * double(dkv) * d.d_ctx));
         dlk::norm_rows(d.norm, out, P(L.normc_g), P(L.normc_b), nbuf, false, T, dm, d.norm_eps, st);
         linear(st, T, nbuf, dm, P(L.w_qc), dm, dq, P(L.b_qc), dlk::EPI_BF16, qkv, dq, nullptr, 0, NormSrc(), nullptr, 0, 0,
-               q_scale, dq);
+               dlk::attention_q_scale(dh), dq);
         // the context is the same for every layer of a pass: layer 0 converts it to bf16 for all of them (a pass
         // always starts at layer 0, and nothing else writes this buffer); ctx_cast = false: an earlier pass of the same
         // call did so
@@ -554,7 +550,7 @@ void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const floa
         linear(st, n_ctx, ctxn, d.d_ctx, P(L.w_kvc), d.d_ctx, 2 * dkv, P(L.b_kvc), dlk::EPI_BF16, kvc, 2 * dkv,
                nullptr, 0, NormSrc(), vtc, dkv, M.W.vtc_ld);
         dlk::QkvPostArgs cp{kvc, 2 * dkv, n_ctx, 0, Hq, Hkv, dh, 0.0f, nullptr, 0, vtc,
-                            uint64_t(dh) * M.W.vtc_ld, M.W.vtc_ld, -1, 0, dkv, 1.0f};
+                            uint64_t(dh) * M.W.vtc_ld, M.W.vtc_ld, -1, 0, dkv};
         dlk::qkv_post(cp, st);
         dlk::AttnArgs ca{qkv, dq, kvc, 2 * dkv, uint64_t(dh), vtc, M.W.vtc_ld, uint64_t(dh) * M.W.vtc_ld, attn, dq,
                          T, n_ctx, 0, Hq, Hkv, dh, 0,

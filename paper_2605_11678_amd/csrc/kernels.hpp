@@ -31,7 +31,9 @@ struct GemmArgs {
     // vt[(n - vt_col) * vt_ld + m] (the V part of a QKV projection straight into the V^T rows attention reads)
     bf16_t* vt;
     int vt_col, vt_ld;
-    // EPI_BF16: columns below scale_cols are multiplied by scale before they are rounded (queries, see attention)
+    // EPI_BF16: columns below scale_cols are multiplied by scale before they are rounded, and before anything else happens to
+    // them (queries, see attention: scaled between two roundings, the second one would count in full where the rotation between
+    // them is next to none)
     float scale;
     int scale_cols;
 };
@@ -48,7 +50,6 @@ struct QkvPostArgs {
     bf16_t* k_out; uint64_t k_head_stride;
     bf16_t* vt_out; uint64_t vt_head_stride; int vt_ld;
     int q_off, k_off, v_off;      // column offsets of q, k, v inside a qkv row (q_off < 0: no q part)
-    float q_scale;                // what a rotated q is multiplied by before it is rounded
 };
 void qkv_post(const QkvPostArgs& a, hipStream_t st);
 // The product and qkv_post in one launch (a.epi = EPI_BF16, a.vt set), where a kernel has that epilogue: at most 64 rows and

@@ -185,9 +185,8 @@ __global__ __launch_bounds__(256) void gemv_kernel(GemvArgs p) {
                 if (q.theta > 0.0f) sincosf(float(pos) * exp2f(-2.0f * float(i) / float(q.dh) * log2f(q.theta)), &sn, &cs);
                 bf16_t* dst = row + r0;                   // Q (q_off = 0) or K kept in the row
                 if (r0 >= dq && q.k_out) dst = q.k_out + size_t((r0 - dq) / q.dh) * q.k_head_stride + size_t(pos) * q.dh + i;
-                const float f = r0 < dq ? q.q_scale : 1.0f;
-                dst[0] = f_to_bf16((a * cs - b * sn) * f);
-                dst[half] = f_to_bf16((a * sn + b * cs) * f);
+                dst[0] = f_to_bf16(a * cs - b * sn);
+                dst[half] = f_to_bf16(a * sn + b * cs);
             }
         } else {
             const float v = acc[u] + (p.bias ? bf16_to_f(p.bias[n]) : 0.0f);

@@ -248,16 +248,16 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
                     a += bf16_to_f(p.bias[r0]);
                     b += bf16_to_f(p.bias[r0 + half]);
                 }
-                a = bf16_to_f(f_to_bf16(a));
-                b = bf16_to_f(f_to_bf16(b));
+                const float f = col_factor(p, r0);
+                a = bf16_to_f(f_to_bf16(a * f));
+                b = bf16_to_f(f_to_bf16(b * f));
                 const int pos = post.pos0 + m;
                 float sn = 0.0f, cs = 1.0f;
                 if (post.theta > 0.0f) sincosf(float(pos) * exp2f(-2.0f * float(i) / float(post.dh) * log2f(post.theta)), &sn, &cs);
-                const float f = hh < n_q ? post.q_scale : 1.0f;
                 bf16_t* dst = static_cast<bf16_t*>(p.out) + size_t(m) * p.ldo + r0;
                 if (hh >= n_q && post.k_out) dst = post.k_out + size_t(hh - n_q) * post.k_head_stride + size_t(pos) * post.dh + i;
-                dst[0] = f_to_bf16((a * cs - b * sn) * f);
-                dst[half] = f_to_bf16((a * sn + b * cs) * f);
+                dst[0] = f_to_bf16(a * cs - b * sn);
+                dst[half] = f_to_bf16(a * sn + b * cs);
             }
             return;
         }
@@ -843,7 +843,8 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
         if (mw + BM / WM <= p.M && nw + BN / WN <= n_end) store_resid_full<TM, TN>(p, acc, mw, nw, lane);
         else store_tiles<EPI, TM, TN>(p, acc, mw, nw, lane, n_end);
     } else {
-        // (a wavefront tile that queries share with keys, or keys with values, goes element by element)
+        // (a tile that keys share with values, or a wavefront tile that queries share with keys, goes element by element: a factor
+        // per column spilled 32 registers of the 256x256 tile)
         const bool mixed = EPI == EPI_BF16 && (n_end > first_vt_col(p) || (nw < p.scale_cols && nw + BN / WN > p.scale_cols));
         if (mixed) store_tiles<EPI, TM, TN>(p, acc, mw, nw, lane, n_end);
         else store_tiles_buf<EPI, TM, TN>(p, acc, mw, nw, lane, n_end);

@@ -207,7 +207,6 @@ __global__ __launch_bounds__(256) void rope_kernel(QkvPostArgs p) {
                 src = row + p.k_off + g * p.dh;
                 dst = p.k_out ? p.k_out + size_t(g) * p.k_head_stride + size_t(pos) * p.dh : row + p.k_off + g * p.dh;
             }
-            const float f = hh < nq ? p.q_scale : 1.0f;
             const u32x4 lo = *reinterpret_cast<const u32x4*>(src + c), hi = *reinterpret_cast<const u32x4*>(src + c + half);
             u32x4 olo, ohi;
 #pragma unroll
@@ -215,8 +214,8 @@ __global__ __launch_bounds__(256) void rope_kernel(QkvPostArgs p) {
                 const float a0 = __uint_as_float(lo[w] << 16), a1 = __uint_as_float(lo[w] & 0xFFFF0000u);
                 const float b0 = __uint_as_float(hi[w] << 16), b1 = __uint_as_float(hi[w] & 0xFFFF0000u);
                 const float c0 = s_cs[c + 2 * w], c1 = s_cs[c + 2 * w + 1], n0 = s_sn[c + 2 * w], n1 = s_sn[c + 2 * w + 1];
-                olo[w] = uint32_t(f_to_bf16((a0 * c0 - b0 * n0) * f)) | (uint32_t(f_to_bf16((a1 * c1 - b1 * n1) * f)) << 16);
-                ohi[w] = uint32_t(f_to_bf16((a0 * n0 + b0 * c0) * f)) | (uint32_t(f_to_bf16((a1 * n1 + b1 * c1) * f)) << 16);
+                olo[w] = uint32_t(f_to_bf16(a0 * c0 - b0 * n0)) | (uint32_t(f_to_bf16(a1 * c1 - b1 * n1)) << 16);
+                ohi[w] = uint32_t(f_to_bf16(a0 * n0 + b0 * c0)) | (uint32_t(f_to_bf16(a1 * n1 + b1 * c1)) << 16);
             }
             *reinterpret_cast<u32x4*>(dst + c) = olo;
             *reinterpret_cast<u32x4*>(dst + c + half) = ohi;
@@ -234,8 +233,8 @@ __global__ __launch_bounds__(256) void rope_kernel(QkvPostArgs p) {
             bf16_t* q = row + p.q_off + h * p.dh;
             for (int ii = i; ii < half; ii += lanes) {
                 const float a = bf16_to_f(q[ii]), b = bf16_to_f(q[ii + half]);
-                q[ii] = f_to_bf16((a * cs - b * sn) * p.q_scale);
-                q[ii + half] = f_to_bf16((a * sn + b * cs) * p.q_scale);
+                q[ii] = f_to_bf16(a * cs - b * sn);
+                q[ii + half] = f_to_bf16(a * sn + b * cs);
             }
         }
     }
