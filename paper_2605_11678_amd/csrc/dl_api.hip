@@ -49,7 +49,9 @@ struct Module {
     PackLayout L;
     dl::WorkspaceLayout W;
     dl::KvLayout KV;
-    uint8_t* store = nullptr;            // n_layers blobs, pinned (or plain malloc in a host-only context)
+    // n_layers blobs, pinned (or plain malloc in a host-only context); with a head, 256 bytes behind them for the token that
+    // dl_logits_argmax's kernel chooses, so that only the logits are copied
+    uint8_t* store = nullptr;
     std::vector<uint32_t> set_mask;      // per layer: which tensors have been provided
     bool finalized = false;
     std::vector<uint8_t> resident;       // per layer
@@ -80,7 +82,6 @@ struct dl_ctx {
     uint8_t* base = nullptr;
     hipStream_t s_compute = nullptr, s_copy = nullptr;
     bool streams_set = false;
-    int32_t* token_host = nullptr;      // pinned: dl_logits_argmax's kernel writes the choice here, so only the logits are copied
     std::vector<Module> mods;
     std::vector<Mlp> mlps;
     uint64_t slot_bytes = 0;
@@ -701,14 +702,6 @@ int32_t dl_create(dl_ctx** out, int32_t device) {
     }
     dl_ctx* c = new dl_ctx();
     c->device = device;
-    if (device >= 0) {
-        void* p = nullptr;
-        if (hipHostMalloc(&p, 256, hipHostMallocDefault) != hipSuccess || !p) {
-            delete c;
-            return DL_ERR_DEVICE;
-        }
-        c->token_host = static_cast<int32_t*>(p);
-    }
     *out = c;
     return DL_OK;
 }
@@ -730,7 +723,6 @@ int32_t dl_destroy(dl_ctx* c) {
             for (int s = 0; s < dl_ctx::kMaxRunAhead; ++s) (void)hipEventDestroy(c->ev_inflight[s]);
         }
         for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
-        (void)hipHostFree(c->token_host);
     }
     for (Module& M : c->mods) {
         if (!M.store) continue;
@@ -822,7 +814,7 @@ int32_t dl_module_create(dl_ctx* c, const dl_module_desc* desc, int32_t* module_
     M.L = dl::make_layout(*desc);
     M.W = dl::make_workspace(*desc);
     M.KV = dl::make_kv(*desc);
-    const uint64_t total = uint64_t(desc->n_layers) * M.L.bytes;
+    const uint64_t total = uint64_t(desc->n_layers) * M.L.bytes + (desc->vocab > 0 ? 256 : 0);   // (see Module::store)
     if (on_gpu(c)) {
         void* p = nullptr;
         if (hipHostMalloc(&p, total, hipHostMallocDefault) != hipSuccess || !p) {
@@ -1048,14 +1040,15 @@ int32_t dl_logits_argmax(dl_ctx* c, int32_t module, const void* h, int32_t* toke
     if (rc) return rc;
     Module* M = get_module(c, module);
     if (!token_out) return fail(c, DL_ERR_INVALID_ARG, "null token_out");
-    rc = head_common(c, M, h, c->token_host);
+    int32_t* const token_host = M && M->d.vocab > 0 ? reinterpret_cast<int32_t*>(M->store + size_t(M->d.n_layers) * M->L.bytes) : nullptr;
+    rc = head_common(c, M, h, token_host);
     if (rc) return rc;
     if (!on_gpu(c)) { *token_out = 0; return DL_OK; }
     uint8_t* ws = c->base + M->ws_off;
     if (logits_out)
         DL_HIP(c, hipMemcpyAsync(logits_out, ws + M->W.logits, 4 * size_t(M->d.vocab), hipMemcpyDeviceToHost, c->s_compute));
     DL_HIP(c, hipStreamSynchronize(c->s_compute));
-    *token_out = *static_cast<volatile int32_t*>(c->token_host);
+    *token_out = *static_cast<volatile int32_t*>(token_host);
     return DL_OK;
 }
 
