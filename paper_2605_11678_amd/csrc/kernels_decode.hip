@@ -433,12 +433,18 @@ void decode_attention(const DecodeAttnArgs& a, hipStream_t st) {
     if (a.S <= 0) return;
     const int n_tiles = (a.S + 63) / 64;
     const float scale_log2 = 1.4426950408889634f / sqrtf(float(a.dh));
-    // One launch for up to four tiles of at most 64 features, one wavefront and SIMD each (partial results within 64 KB of LDS).
-    // Four layers of the tiny decoder, passes queued: 82 .. 88 us over 40 .. 250 positions with two launches each, 77 .. 81 with one; over
-    // 900 positions (16 wavefronts) one launch was slower, 105 against 84 .. 88, and so it was for one 8B layer over 300
-    // positions of 128 features, 83.4 against 80.9.
-    const size_t lds = size_t(a.Hq / a.Hkv) * n_tiles * (a.dh + 2) * 4;
-    if (a.dh <= 64 && n_tiles <= 4 && lds <= 64 * 1024) {
+    // One launch for up to four tiles of at most 64 features, one wavefront and SIMD each, while the merge stays short: one
+    // workgroup of a KV head merges all of its query heads, where the second launch has one each.  Four layers of 256 features,
+    // passes queued, us a pass, one launch / two (these by the build 83 or 85 .. 90), by heads (query, KV) x features and positions:
+    //   4, 4 x 64: 76 / 82 over 40, 77 / 81 over 250;   16, 2 x 64: 80.5 / 83 over 180, 83.3 / 83 .. 88 over 250;
+    //   32, 4 x 64: 83.6 / 84 over 180, 85.8 / 84 .. 90 over 250;   16, 1 x 32: 78.4 / 80 .. 87 over 250;
+    //   32, 2 x 64: 84.5 / 87 over 40, 85.2 / 84 .. 90 over 100, 86.6 / 83 .. 89 over 180, 88.8 / 84 .. 89 over 250;
+    //   32, 1 x 64: 90 / 86 .. 88 over 40, 92 / 84 .. 87 over 100, 99 / 83 .. 87 over 250.
+    // So the line is what the workgroup merges: the head group's outputs, times the tiles that each folds.  Over 900 positions
+    // (16 wavefronts) one launch took 105 against 84 .. 88, and one 8B layer over 300 positions of 128 features 83.4 against 80.9.
+    const int group = a.Hq / a.Hkv;
+    if (a.dh <= 64 && n_tiles <= 4 && group * a.dh <= 1024 && group * a.dh * n_tiles <= 2048) {
+        const size_t lds = size_t(group) * n_tiles * (a.dh + 2) * 4;          // at most 10 KB (dh >= 8)
         hipLaunchKernelGGL((decode_attn_short<64, 4>), dim3(a.Hkv), dim3(256), lds, st, a, scale_log2, n_tiles);
         return;
     }

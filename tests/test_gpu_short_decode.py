@@ -1,6 +1,6 @@
 """Single-token attention over few cached positions (one launch, one workgroup per KV head) on both sides of the switch to the
-two-launch form: one tile, ragged tiles, the last length that takes it and the first that does not, for each padded head
-dimension, grouped and ungrouped heads; against the oracle, the feed-forward zeroed."""
+two-launch form: one tile, ragged tiles, the last length and the largest head group that take it and the first that do not, for each
+padded head dimension, grouped and ungrouped heads; against the oracle, the feed-forward zeroed."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-2
 
 # (Hq, Hkv, dh, cached positions before the token)
-CASES = [(4, 4, 64, s) for s in (0, 1, 62, 63, 64, 200, 254, 255, 256)] + [(8, 2, 40, 129), (3, 3, 72, 63), (8, 2, 128, 200), (32, 1, 64, 255)]
+CASES = [(4, 4, 64, s) for s in (0, 1, 62, 63, 64, 200, 254, 255, 256)] + [(8, 2, 40, 129), (3, 3, 72, 63), (8, 2, 128, 200), (32, 1, 64, 255), (16, 1, 64, 62),
+                                                                                       (17, 1, 64, 62), (32, 2, 64, 127), (32, 2, 64, 128), (32, 1, 32, 130), (32, 1, 8, 255)]
 
 
 @pytest.mark.parametrize("Hq,Hkv,dh,prefix", CASES)
