@@ -464,6 +464,9 @@ __device__ __forceinline__ void store_tiles(const GemmArgs& p, f32x16 (&acc)[TM]
 // written, columns past the tile's get an offset that is, so nothing is predicated, and an element costs its arithmetic, its
 // conversion and the store; a row's scalar offset is computed once for all of its column tiles, which are stored together.
 // (host: the 128 rows of a wavefront tile span less than 2 GB)
+// (the largest wavefront tile has no registers for a factor per column, 32 would spill: one for all of its columns, see the caller)
+template <int TM, int TN>
+constexpr bool kColFactors = TM * TN < 16;
 template <int EPI, int TM, int TN>
 __device__ __forceinline__ void store_tiles_buf(const GemmArgs& p, f32x16 (&acc)[TM][TN], int mw, int nw, int lane, int n_end) {
     constexpr bool SW = EPI == EPI_SWIGLU_BF16;
@@ -473,13 +476,13 @@ __device__ __forceinline__ void store_tiles_buf(const GemmArgs& p, f32x16 (&acc)
     const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
         static_cast<uint8_t*>(p.out) + (size_t(mw) * p.ldo + (SW ? nw / 2 : nw)) * E, 0, int(uint32_t(rows) * uint32_t(p.ldo) * E), kBufferFlags);
     uint32_t off[TN];
-    float bias[TN];
-    const float f = EPI == EPI_BF16 ? col_factor(p, nw) : 1.0f;      // the same for all columns (see the caller)
+    float bias[TN], f[TN];
 #pragma unroll
     for (int j = 0; j < TN; j += JS) {
         const int n = nw + 32 * j + col_in;              // SwiGLU: the gate column, its up column is 32 further on
         off[j] = n + 32 * (JS - 1) < n_end ? uint32_t(row_in * p.ldo + 32 * (j / JS) + col_in) * E : 0x80000000u;
-        bias[j] = !SW && p.bias ? bf16_to_f(p.bias[min(n, n_end - 1)]) * f : 0.0f;
+        f[j] = EPI == EPI_BF16 ? col_factor(p, kColFactors<TM, TN> ? n : nw) : 1.0f;
+        bias[j] = !SW && p.bias ? bf16_to_f(p.bias[min(n, n_end - 1)]) * f[j] : 0.0f;
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -491,7 +494,7 @@ __device__ __forceinline__ void store_tiles_buf(const GemmArgs& p, f32x16 (&acc)
                 if constexpr (SW) {
                     __builtin_amdgcn_raw_buffer_store_b16(f_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 1][r]), out, int(off[j]), so, 0);
                 } else {
-                    const float v = EPI == EPI_BF16 ? fmaf(acc[i][j][r], f, bias[j]) : acc[i][j][r] + bias[j];
+                    const float v = EPI == EPI_BF16 ? fmaf(acc[i][j][r], f[j], bias[j]) : acc[i][j][r] + bias[j];
                     if constexpr (EPI == EPI_F32) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, int(off[j]), so, 0);
                     else __builtin_amdgcn_raw_buffer_store_b16(f_to_bf16(EPI == EPI_GELU_BF16 ? gelu_tanh_f(v) : v), out, int(off[j]), so, 0);
                 }
@@ -843,9 +846,10 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
         if (mw + BM / WM <= p.M && nw + BN / WN <= n_end) store_resid_full<TM, TN>(p, acc, mw, nw, lane);
         else store_tiles<EPI, TM, TN>(p, acc, mw, nw, lane, n_end);
     } else {
-        // (a tile that keys share with values, or a wavefront tile that queries share with keys, goes element by element: a factor
-        // per column spilled 32 registers of the 256x256 tile)
-        const bool mixed = EPI == EPI_BF16 && (n_end > first_vt_col(p) || (nw < p.scale_cols && nw + BN / WN > p.scale_cols));
+        // (a tile that keys share with values goes element by element, and where there is one factor for all columns of a
+        // wavefront tile, one that queries share with keys)
+        const bool mixed = EPI == EPI_BF16 && (n_end > first_vt_col(p) ||
+                                               (!kColFactors<TM, TN> && nw < p.scale_cols && nw + BN / WN > p.scale_cols));
         if (mixed) store_tiles<EPI, TM, TN>(p, acc, mw, nw, lane, n_end);
         else store_tiles_buf<EPI, TM, TN>(p, acc, mw, nw, lane, n_end);
     }
