@@ -344,6 +344,14 @@ void launch_few_rows(const GemmArgs& a, hipStream_t st, const PostArgs<EPI>& pos
     else go(c64, c16, integral_constant<int, 2>{});
 }
 
+// Column tiles whose residual values are requested together: what fits next to the accumulators without spilling (TM = 3: all of
+// them).  The 256x192 tile takes one at a time: two spilled 32 registers and took 169.0 us for 4096 x 4096 outputs, K = 4096, now
+// 164.1; 472.8 for 3072 x 4096, K = 12288, now 456.4; 33.8 for 8192 x 1152, K = 1152, now 31.5.
+constexpr int resid_batch(int tm, int tn) {
+    const int fit = (300 - tm * tn * 16) / (tm * 16);
+    return tm == 3 ? tn : (fit < 1 ? 1 : (fit > tn ? tn : fit));
+}
+
 // epilogue shared by the tiled kernels: accumulator tile (i, j) of a wavefront whose tile starts at (mw, nw)
 // n_end: first column past the tile's own columns (the matrix edge, or the start of the next tile when the tile's
 // LDS width is padded beyond its stride)
@@ -375,9 +383,7 @@ __device__ __forceinline__ void store_tiles(const GemmArgs& p, f32x16 (&acc)[TM]
         // wavefront pays one memory round trip per batch instead of one per tile; only the stores are predicated.
         const float* __restrict__ resid = p.resid;
         float* __restrict__ out = static_cast<float*>(p.out);
-        // column tiles per batch: what fits next to the accumulators without spilling (TM = 3: all of them)
-        constexpr int JFIT = (352 - TM * TN * 16) / (TM * 16);
-        constexpr int JB = TM == 3 ? TN : (JFIT < 1 ? 1 : (JFIT > TN ? TN : JFIT));
+        constexpr int JB = resid_batch(TM, TN);
 #pragma unroll
         for (int j0 = 0; j0 < TN; j0 += JB) {
             float rv[JB][TM][16];
@@ -515,8 +521,7 @@ __device__ __forceinline__ void store_resid_full(const GemmArgs& p, f32x16 (&acc
     const float* __restrict__ resid = p.resid + size_t(mw) * p.ldr + nw;
     float* __restrict__ out = static_cast<float*>(p.out) + size_t(mw) * p.ldo + nw;
     const uint32_t lane_r = row_in * uint32_t(p.ldr) + col_in;
-    constexpr int JFIT = (352 - TM * TN * 16) / (TM * 16);
-    constexpr int JB = TM == 3 ? TN : (JFIT < 1 ? 1 : (JFIT > TN ? TN : JFIT));
+    constexpr int JB = resid_batch(TM, TN);
 #pragma unroll
     for (int j0 = 0; j0 < TN; j0 += JB) {
         float rv[JB][TM][16];
@@ -939,28 +944,28 @@ struct TileShape {
     float step, edge[EPI_F32 + 1];                       // by epilogue: plain, residual, SwiGLU, GELU, fp32
 };
 constexpr TileShape kTiles[] = {
-    {256, 256, 2, 1.436f, {6.0f, 13.2f, 5.3f, 11.6f, 7.1f}}, {192, 256, 2, 1.229f, {4.5f, 6.8f, 3.4f, 9.0f, 3.0f}},
-    {256, 192, 2, 1.189f, {6.1f, 15.9f, 6.1f, 9.4f, 7.6f}},  {128, 256, 3, 0.803f, {6.0f, 8.1f, 4.7f, 9.3f, 6.8f}},
-    {192, 192, 3, 0.862f, {9.4f, 11.9f, 9.4f, 8.4f, 6.7f}},  {192, 128, 4, 0.627f, {4.9f, 8.6f, 4.6f, 7.2f, 7.4f}},
-    {128, 192, 2, 1.390f, {0.5f, 3.7f, 0.5f, 2.4f, 3.5f}},   {128, 128, 2, 1.000f, {1.2f, 2.9f, 1.0f, 3.8f, 1.6f}},
-    {128, 160, 4, 0.661f, {4.0f, 6.4f, 4.0f, 5.8f, 3.0f}},   {128, 128, 5, 0.551f, {1.6f, 2.8f, 2.0f, 3.1f, 1.6f}},
-    {128, 96, 5, 0.396f, {3.3f, 5.5f, 3.3f, 4.5f, 4.3f}},    {128, 64, 6, 0.335f, {1.9f, 3.3f, 1.9f, 2.8f, 1.8f}},
-    {64, 128, 6, 0.419f, {1.5f, 1.5f, 1.4f, 2.5f, 1.2f}},    {64, 64, 8, 0.261f, {1.3f, 1.6f, 1.3f, 1.9f, 1.0f}},
+    {256, 256, 2, 1.438f, {5.5f, 13.1f, 5.4f, 11.1f, 6.7f}}, {192, 256, 2, 1.246f, {4.7f, 8.8f, 3.1f, 8.7f, 2.2f}},
+    {256, 192, 2, 1.156f, {6.6f, 10.4f, 6.6f, 9.9f, 9.4f}},  {128, 256, 3, 0.809f, {5.7f, 8.0f, 4.6f, 9.2f, 6.6f}},
+    {192, 192, 3, 0.867f, {9.4f, 11.9f, 9.4f, 8.3f, 6.4f}},  {192, 128, 4, 0.632f, {4.8f, 8.5f, 4.5f, 7.2f, 7.3f}},
+    {128, 192, 2, 1.362f, {0.8f, 4.2f, 0.8f, 2.9f, 4.0f}},   {128, 128, 2, 1.008f, {1.1f, 2.8f, 0.9f, 3.8f, 1.4f}},
+    {128, 160, 4, 0.666f, {3.9f, 6.3f, 3.9f, 5.7f, 2.9f}},   {128, 128, 5, 0.553f, {1.5f, 2.7f, 1.9f, 3.0f, 1.5f}},
+    {128, 96, 5, 0.397f, {3.2f, 5.4f, 3.2f, 4.5f, 4.3f}},    {128, 64, 6, 0.335f, {1.9f, 3.2f, 1.9f, 2.7f, 1.7f}},
+    {64, 128, 6, 0.419f, {1.5f, 1.4f, 1.3f, 2.4f, 1.1f}},    {64, 64, 8, 0.261f, {1.3f, 1.6f, 1.3f, 1.8f, 1.0f}},
 };
 // gate/up pairs sit in one wavefront: an even number of 32-wide tile columns per wavefront
 constexpr bool even_cols(const TileShape& t) { return t.bn % 128 == 0; }
 
 // A last round with a fraction x of its workgroups takes less than a whole one (they have the chip to themselves, and behind
-// other rounds they do not start together): 0.71 + 0.29 x; 0.79 where two workgroups share a compute unit and at most every other
-// place is taken (x <= 1/2), from there up to 1; the split tail 0.73.  Fitted with the table above.
+// other rounds they do not start together): 0.71 + 0.29 x; 0.79, less behind full rounds, where two workgroups share a compute unit
+// and at most every other place is taken (x <= 1/2), from there up to 1; the split tail 0.71.  Fitted with the table above.
 float rounds_of(const TileShape& t, int M, int N) {
     const long tiles = long((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
     const bool two = two_per_cu(t.bm, t.bn, t.ns);
     const long slots = two ? 512 : 256, full = tiles / slots, rest = tiles % slots;
     if (rest == 0) return float(full);
-    if (t.bm == 256 && t.bn == 256 && splits_tail(tiles)) return float(full) + 0.73f;
+    if (t.bm == 256 && t.bn == 256 && splits_tail(tiles)) return float(full) + 0.71f;
     const float x = float(rest) / float(slots);
-    const float least = two ? 0.79f / (1.0f + 0.16f * float(full)) : 0.71f / (1.0f + 0.01f * float(full));
+    const float least = two ? 0.79f / (1.0f + 0.21f * float(full)) : 0.71f;
     const float part = two ? (x > 0.5f ? 2.0f * x - 1.0f : 0.0f) : x;
     return float(full) + least + (1.0f - least) * part;
 }
