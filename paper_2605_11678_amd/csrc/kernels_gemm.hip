@@ -469,7 +469,7 @@ __device__ __forceinline__ void store_tiles(const GemmArgs& p, f32x16 (&acc)[TM]
 // there).  The others go through a buffer over the wavefront tile's rows of the output: rows past M are out of range and not
 // written, columns past the tile's get an offset that is, so nothing is predicated, and an element costs its arithmetic, its
 // conversion and the store; a row's scalar offset is computed once for all of its column tiles, which are stored together.
-// (host: the 128 rows of a wavefront tile span less than 2 GB)
+// (host: the rows of a wavefront tile span less than 2 GB)
 // (the largest wavefront tile has no registers for a factor per column, 32 would spill: one for all of its columns, see the caller)
 template <int TM, int TN>
 constexpr bool kColFactors = TM * TN < 16;
@@ -942,6 +942,8 @@ void launch_fast(const GemmArgs& a, hipStream_t st) {
 struct TileShape {
     int bm, bn, ns;
     float step, edge[EPI_F32 + 1];                       // by epilogue: plain, residual, SwiGLU, GELU, fp32
+    // 96 and 160 columns are an odd number of MFMA tiles: the four wavefronts are stacked in M there
+    constexpr int waves_m() const { return bn % 64 ? 4 : 2; }
 };
 constexpr TileShape kTiles[] = {
     {256, 256, 2, 1.438f, {5.5f, 13.1f, 5.4f, 11.1f, 6.7f}}, {192, 256, 2, 1.246f, {4.7f, 8.8f, 3.1f, 8.7f, 2.2f}},
@@ -970,13 +972,15 @@ float rounds_of(const TileShape& t, int M, int N) {
     return float(full) + least + (1.0f - least) * part;
 }
 
-int pick_tile(int M, int N, int K, int epi) {
+// ldo: the rows of a wavefront tile must span less than 2 GB, 4 bytes an element (wider outputs take the lower tiles; there is
+// always the 64 rows of 128x128 on two stages)
+int pick_tile(int M, int N, int K, int ldo, int epi) {
     const int nk = K / 64;
     int best = 0;
     float best_cost = 1e30f;
     for (int c = 0; c < int(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
         const TileShape& t = kTiles[c];
-        if (nk < t.ns || (epi == EPI_SWIGLU_BF16 && !even_cols(t))) continue;
+        if (nk < t.ns || (epi == EPI_SWIGLU_BF16 && !even_cols(t)) || size_t(t.bm / t.waves_m()) * size_t(ldo) >= (1u << 29)) continue;
         const float cost = rounds_of(t, M, N) * (t.edge[epi] + float(nk) * t.step);
         if (cost < best_cost) { best_cost = cost; best = c; }
     }
@@ -988,14 +992,13 @@ void dispatch_fast(int c, const GemmArgs& a, hipStream_t st) {
     if constexpr (C < int(sizeof(kTiles) / sizeof(kTiles[0]))) {
         constexpr TileShape t = kTiles[C];
         if (c != C) return dispatch_fast<EPI, C + 1>(c, a, st);
-        // 96 and 160 columns are an odd number of MFMA tiles: the four wavefronts are stacked in M there
-        if constexpr (EPI != EPI_SWIGLU_BF16 || even_cols(t)) launch_fast<t.bm, t.bn, EPI, t.bn % 64 ? 4 : 2, t.ns>(a, st);
+        if constexpr (EPI != EPI_SWIGLU_BF16 || even_cols(t)) launch_fast<t.bm, t.bn, EPI, t.waves_m(), t.ns>(a, st);
     }
 }
 
 template <int EPI>
 void dispatch_fast(const GemmArgs& a, hipStream_t st) {
-    dispatch_fast<EPI>(pick_tile(a.M, a.N, a.K, EPI), a, st);
+    dispatch_fast<EPI>(pick_tile(a.M, a.N, a.K, a.ldo, EPI), a, st);
 }
 
 bool takes_tiles(const GemmArgs& a) {
@@ -1004,7 +1007,7 @@ bool takes_tiles(const GemmArgs& a) {
     // (33 .. 64 rows over more than 8192 columns: a 64-row tile of this path reads A for 64 or 128 columns at a time, and
     // there are enough such tiles; 24576 x 4096 gate/up, 64 rows: 54 us with the few-rows kernel, 44 with 64x128 tiles)
     return a.K >= 128 && a.K % 128 == 0 && a.lda % 8 == 0 && a.ldb % 8 == 0 &&
-                      (a.M > 64 || (a.M > 32 && a.N > 8192)) && a.N >= 64 && a.ldo < (1 << 22) &&
+                      (a.M > 64 || (a.M > 32 && a.N > 8192)) && a.N >= 64 && a.ldo < (1 << 23) &&
                       size_t(a.M) * a.lda * 2 < (1ull << 32) && size_t(a.N) * a.ldb * 2 < (1ull << 32);
 }
 
@@ -1079,10 +1082,17 @@ void gemm(const GemmArgs& a, hipStream_t st) {
 
 }  // namespace dlk
 
-// For tests (host only): the tile shape that the dispatcher takes for a product of the fast path.
-extern "C" __attribute__((visibility("default"))) void dlk_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t* bm, int32_t* bn, int32_t* stages) {
-    const dlk::TileShape& t = dlk::kTiles[dlk::pick_tile(M, N, K, epi)];
+// For tests (host only): whether a product with contiguous operands takes the LDS-staged tiles, and which.
+extern "C" __attribute__((visibility("default"))) int32_t dlk_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t* bm, int32_t* bn, int32_t* stages) {
+    dlk::GemmArgs a{};
+    a.lda = a.ldb = a.K = K;
+    a.ldo = epi == dlk::EPI_SWIGLU_BF16 ? N / 2 : N;
+    a.M = M;
+    a.N = N;
+    if (!dlk::takes_tiles(a)) return 0;
+    const dlk::TileShape& t = dlk::kTiles[dlk::pick_tile(M, N, K, a.ldo, epi)];
     *bm = t.bm;
     *bn = t.bn;
     *stages = t.ns;
+    return 1;
 }

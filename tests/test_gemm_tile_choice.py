@@ -12,8 +12,8 @@ GOLDEN = os.path.join(os.path.dirname(__file__), "golden", "gemm_tile_times.npz"
 
 def tile_of(M, N, K, epi):
     out = [C.c_int32() for _ in range(3)]
-    B.lib().dlk_gemm_tile(int(M), int(N), int(K), int(epi), *[C.byref(v) for v in out])
-    return tuple(v.value for v in out)
+    ok = B.lib().dlk_gemm_tile(int(M), int(N), int(K), int(epi), *[C.byref(v) for v in out])
+    return tuple(v.value for v in out) if ok else None
 
 
 def test_choice_against_measured_times():
@@ -28,3 +28,14 @@ def test_choice_against_measured_times():
     # and over each epilogue alone
     for e in range(5):
         assert np.exp(np.mean(np.log(loss[z["problems"][:, 3] == e]))) <= 1.015, e
+
+
+def test_wide_outputs_take_the_tiles():
+    """Rows of 2^22 elements and more as well, on tiles whose wavefronts' rows span less than 2 GB; which products never do."""
+    for N in (64, 4096, (1 << 22) - 64, 1 << 22, (1 << 22) + 192, (1 << 23) - 64):
+        for M in (66, 1000):
+            for K in (128, 256):
+                for epi in (0, 1, 3, 4):
+                    bm, bn, _ = tile_of(M, N, K, epi)
+                    assert bm // (4 if bn % 64 else 2) * N * 4 < 1 << 31, (M, N, K, epi)
+    assert tile_of(66, 1 << 23, 256, 3) is None and tile_of(66, 4096, 192, 3) is None and tile_of(32, 4096, 256, 3) is None

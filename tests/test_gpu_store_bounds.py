@@ -120,3 +120,26 @@ def test_cache_rows(d, Hq, Hkv, dh, prefix, T):
         assert not changed.any()
     finally:
         g.close()
+
+
+def test_rows_of_four_million():
+    """An output whose rows are longer than 2^22 elements, on LDS-staged tiles, and the reduction over them.  The weights repeat 64 times,
+    so one period is the oracle's."""
+    T, d_in, period, reps, d_out = 66, 128, 65544, 64, 64
+    w1, b1, w2, b2 = CFG.make_mlp(d_in, period, d_out, seed=4321)
+    x = CFG.make_tokens(T, d_in, seed=18)
+    d_hid = reps * period
+    eng = Engine(2 * (d_hid * (d_in + d_out + 1) + T * (d_in + d_hid)) + 4 * T * (d_in + d_out) + (64 << 20), device=0)
+    try:
+        m = eng.ctx.mlp_create(d_in, d_hid, d_out, np.tile(w1, (reps, 1)), np.tile(b1, reps), np.tile(w2, (1, reps)), b2, max_tokens=T)
+        xp, xv = eng.alloc_f32(T * d_in)
+        yp, yv = eng.alloc_f32(T * d_out)
+        eng.upload(xv, x)
+        eng.ctx.mlp_forward(m, xp, yp, T)
+        got = eng.download(yv).reshape(T, d_out)
+    finally:
+        eng.close()
+    rows = [0, 1, 31, 32, 63, 64, 65]
+    bias = F.widen(b2)
+    want = reps * (PL.mlp(x[rows], w1, b1, w2, b2) - bias) + bias
+    assert rel_err(got[rows], want) <= TOL
