@@ -1,8 +1,11 @@
 """Shared helpers of the GPU parity tests: run a stack through the C ABI, run the oracle on the
 same seeded inputs, compare."""
+import ctypes as C
+
 import numpy as np
 
 from oracle import forward as F
+from paper_2605_11678_amd import binding as B
 from paper_2605_11678_amd import configs as CFG
 from paper_2605_11678_amd.harness import Engine
 
@@ -10,6 +13,14 @@ from paper_2605_11678_amd.harness import Engine
 def rel_err(got, want):
     """max |got - want| / max |want| (element-wise ratios are meaningless near zero)."""
     return float(np.max(np.abs(got.astype(np.float64) - want)) / np.max(np.abs(want)))
+
+
+def tile_of(M, N, K, epi):
+    """(rows, columns, LDS stages) of the tile that the GEMM dispatcher takes, None where another kernel runs (host only).
+    epi: 0 plain, 1 residual, 2 SwiGLU, 3 GELU, 4 fp32."""
+    out = [C.c_int32() for _ in range(3)]
+    ok = B.lib().dlk_gemm_tile(int(M), int(N), int(K), int(epi), *[C.byref(v) for v in out])
+    return tuple(v.value for v in out) if ok else None
 
 
 def oracle_cfg(c):

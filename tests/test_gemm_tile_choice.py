@@ -1,19 +1,12 @@
 """The tile shape that the GEMM dispatcher takes, against the measured times of every shape (MI355X, us per launch, launches in a row with
 cold weights) on 810 problems (rows, columns, reduction, epilogue).  Host only: the times are stored, the choice is the library's."""
-import ctypes as C
 import os
 
 import numpy as np
 
-from paper_2605_11678_amd import binding as B
+from tests.gpu_common import tile_of
 
 GOLDEN = os.path.join(os.path.dirname(__file__), "golden", "gemm_tile_times.npz")
-
-
-def tile_of(M, N, K, epi):
-    out = [C.c_int32() for _ in range(3)]
-    ok = B.lib().dlk_gemm_tile(int(M), int(N), int(K), int(epi), *[C.byref(v) for v in out])
-    return tuple(v.value for v in out) if ok else None
 
 
 def test_choice_against_measured_times():

@@ -7,7 +7,7 @@ import pytest
 
 from oracle import forward as F
 from paper_2605_11678_amd import configs as CFG
-from tests.gpu_common import GpuStack
+from tests.gpu_common import GpuStack, tile_of
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-2          # bf16 operands, as the other block tests
@@ -32,16 +32,33 @@ def test_encoder_block(d, Hq, Hkv, dh, T):
     g = GpuStack(c, max_tokens=T, cap_bytes=512 << 20, weights=lambda l: w)
     try:
         got = g.forward(x)
-        few = g.forward(x[:2])                         # another kernel, the same sums
+        few = g.forward(x[:2])                         # the few-rows or the register-staged kernel
     finally:
         g.close()
     assert np.max(np.abs(got - want)) / np.max(np.abs(want - x)) <= TOL
-    assert np.all(np.isfinite(few))
+    want = F.stack_forward(c.as_dict(), lambda l: w, x[:2])
+    assert np.max(np.abs(few - want)) / np.max(np.abs(want - x[:2])) <= TOL
 
 
 @pytest.mark.parametrize("prefix,T", [(1, 2), (3, 19), (8, 64), (5, 67), (130, 131), (7, 517)])
 def test_chunk_at_unaligned_position(prefix, T):
-    c = CFG.ModuleConfig("dec", 1, 128, 8, 2, 40, 256, CFG.NORM_RMS, CFG.ACT_SWIGLU, 0, 1, 1e6, max_seq=prefix + T + 5, seed_base=5200)
+    _chunk(CFG.ModuleConfig("dec", 1, 128, 8, 2, 40, 256, CFG.NORM_RMS, CFG.ACT_SWIGLU, 0, 1, 1e6, max_seq=prefix + T + 5, seed_base=5200), prefix, T)
+
+
+# (d_model, Hq, Hkv, dh, prefix, tokens): column tiles that are all V, the last one ragged; their rows are stored from transposed
+# accumulators
+WHOLE = [(512, 6, 6, 40, 5, 67), (512, 6, 6, 72, 7, 300), (1024, 5, 5, 120, 3, 517), (1152, 16, 16, 72, 1, 731)]
+
+
+@pytest.mark.parametrize("d,Hq,Hkv,dh,prefix,T", WHOLE)
+def test_chunk_with_tiles_of_v_alone(d, Hq, Hkv, dh, prefix, T):
+    n, v0 = (Hq + 2 * Hkv) * dh, (Hq + Hkv) * dh
+    bn = tile_of(T, n, d, 0)[1]
+    assert -(-v0 // bn) * bn < n and (n % bn or d == 1152)
+    _chunk(CFG.ModuleConfig("dec", 1, d, Hq, Hkv, dh, 256, CFG.NORM_RMS, CFG.ACT_SWIGLU, 0, 1, 1e6, max_seq=prefix + T + 5, seed_base=5250), prefix, T)
+
+
+def _chunk(c, prefix, T):
     w = attention_only(c)
     x = CFG.make_tokens(prefix + T, c.d_model, seed=43)
     want = F.stack_forward(c.as_dict(), lambda l: w, x)
