@@ -98,13 +98,11 @@ struct AttnArgs {
     bf16_t* out; int ldo;                             // out + t*ldo + h*dh
     int T, S, q_pos0, Hq, Hkv, dh, causal;
     // optional scratch for calls with at most 128 queries and at least 512 keys: the key range is then split over more
-    // workgroups, as far as the scratch goes, and the pieces are merged by a second launch (fixed order).  nullptr: never
-    // split.
+    // workgroups, as far as the scratch goes (Hq * T * (DV + 4) floats a run, DV = dh rounded up to 64, 96 or 128; at most 16
+    // runs), and the pieces are merged by a second launch (fixed order).  nullptr: never split.
     float* split_ws;
     uint64_t split_ws_bytes;
 };
-// bytes of split_ws that let a call with T queries (T <= 128) split its key range
-uint64_t attention_split_workspace_bytes(int T, int Hq, int dh);
 void attention(const AttnArgs& a, hipStream_t st);
 
 // Single-query attention over a KV cache (decode), split over the key range: one wavefront per

@@ -401,7 +401,7 @@ __global__ __launch_bounds__(128) void attn_merge_kernel(AttnArgs p, int n_runs)
 // At most 128 queries over at least 512 keys: the key range is cut over the z dimension, into runs of at least two tiles, as
 // many as give every compute unit a workgroup, at most 16, and no more than the scratch holds.  19 queries of 32 heads over
 // 3091 cached keys: 8 workgroups walked 49 tiles each in 62 us; 32 workgroups in 4 runs (what the scratch holds) and the
-// merge take 22 + 5.
+// merge take 18 + 5.
 template <int DK, int DV, bool ONES>
 void launch_attn(const AttnArgs& a, hipStream_t st) {
     const int group = a.Hq / a.Hkv;
@@ -429,12 +429,6 @@ void launch_attn(const AttnArgs& a, hipStream_t st) {
 }
 
 }  // namespace
-
-uint64_t attention_split_workspace_bytes(int T, int Hq, int dh) {
-    const int dhp = dh <= 64 ? 64 : (dh <= 96 ? 96 : 128);
-    const uint64_t t = T < 128 ? T : 128;
-    return 16ull * uint64_t(Hq) * t * uint64_t(dhp + 4) * 4;
-}
 
 void attention(const AttnArgs& a, hipStream_t st) {
     if (a.T <= 0 || a.S <= 0) return;

@@ -325,10 +325,11 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
     }
 }
 
-// Two workgroups per compute unit (at most 80 KB of LDS), so that one's start and end hide under the other's stream; also
-// where there are not that many workgroups, more stages gain nothing.  Columns per workgroup: 16; 32 for 33 .. 64 rows
-// where 16 would be more than one workgroup per compute unit (6144 x 4096, 64 rows: 23 -> 19 us; up to 32 rows A is too
-// small a share of the traffic: 24576 x 4096, 19 rows: 39 with 16 columns, 41 with 32).
+// Stages for two workgroups per compute unit (64, 72 or 80 KB of LDS), so that one's start and end hide under the other's stream;
+// also where there are not that many workgroups, more stages gain nothing.  Columns per workgroup: 16; 32 for 33 .. 64 rows
+// where 16 would be more than one workgroup per compute unit (6144 x 4096, 64 rows: 23 -> 19 us, with three stages in 144 KB and
+// one workgroup per compute unit; up to 32 rows A is too small a share of the traffic: 24576 x 4096, 19 rows: 39 with 16 columns, 41
+// with 32).
 template <int EPI>
 void launch_few_rows(const GemmArgs& a, hipStream_t st, const PostArgs<EPI>& post = {}) {
     auto go = [&](auto bm, auto bn, auto ns) {
@@ -353,8 +354,7 @@ constexpr int resid_batch(int tm, int tn) {
 }
 
 // epilogue shared by the tiled kernels: accumulator tile (i, j) of a wavefront whose tile starts at (mw, nw)
-// n_end: first column past the tile's own columns (the matrix edge, or the start of the next tile when the tile's
-// LDS width is padded beyond its stride)
+// n_end: first column past the tile's own columns (the start of the next tile or the matrix edge)
 template <int EPI, int TM, int TN>
 __device__ __forceinline__ void store_tiles(const GemmArgs& p, f32x16 (&acc)[TM][TN], int mw, int nw, int lane, int n_end) {
     const int col_in = lane & 31, row_in = (lane >> 5) * 4;
@@ -777,8 +777,8 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     // and meets the others at the one barrier of the k-tile; past it (a) k-tile kt+1 has landed for everyone and
     // (b) nobody reads stage kt any more, so the copy of k-tile kt+NS into that stage starts right there: its A half
     // is spread over the last phase, its B half over the first phase of the next k-tile.  With NS = 2 stages a copy has
-    // one k-tile of MFMAs to land (64 per wavefront for the large tiles: enough); a small tile's k-tile is 16-20 MFMAs,
-    // so it runs NS = 4 stages and its copies have three k-tiles.
+    // one k-tile of MFMAs to land (64 per wavefront for the large tiles: enough); a smaller tile's k-tile is 4 to 36 MFMAs a
+    // wavefront, so it runs three to eight stages and its copies have two to seven k-tiles.
     // REM = k-tiles after this one, capped at NS (the steady state): with fewer than NS - 1 left the copy's B half has
     // nothing to fetch, with fewer than NS its A half; the wait leaves the copies younger than k-tile kt+1 in flight.
     auto ktile = [&](bf16_t* cur, bf16_t* nxt, bf16_t* prv, int kt, auto rem_c) {
