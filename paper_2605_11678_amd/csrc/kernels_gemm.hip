@@ -933,7 +933,7 @@ void launch_fast(const GemmArgs& a, hipStream_t st) {
 // 7 %; the shape taken is 0.5 % (geometric mean) slower than the fastest, 1.7 % of the problems lose more than 10 %.  Fitted
 // without 342 of the problems, the choice loses 0.9 % on these.  (A table fitted to M up to 4096 without a column for the residual,
 // with one entry set by hand, and blind to the split tail, lost 3.0 % on all and 3.4 % on these: 4096 x 1152 residual outputs, K =
-// 1152, 25.8 us where 128x128 tiles take 20.0; K = 4352, 51.6 where 192x128 take 46.4.)
+// 1152, 23.4 us where 128x128 tiles take 20.0; K = 4352, 51.6 where 192x128 take 46.4.)
 // What separates the shapes: a compute unit takes in about 40 bytes per clock through the global -> LDS path whatever the tile,
 // so large tiles need fewer bytes per flop and win as soon as there are rounds of them; and a copy takes up to ~1.3 us to
 // land (weights cold), more than a small tile's k-tile lasts, so tiles of at most 128x160 run on four to eight stages
