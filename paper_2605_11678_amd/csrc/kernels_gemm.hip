@@ -929,8 +929,8 @@ void launch_fast(const GemmArgs& a, hipStream_t st) {
 // unit (two where they share it), edge what a tile spends outside its main loop with each epilogue, step the time of one 64-deep
 // k-tile with all compute units busy, in us.  The constants are one fit to the times of every shape on 810 problems (M 66 .. 16384
 // against 36 outputs of 256 .. 24576 columns and reductions of 256 .. 12288, weights cold, as launches in a row), weighted to
-// the shapes that come near the fastest; an added constant for the launch (1.8) is left out, being the same for all.  Median error
-// 7 %; the shape taken is 0.5 % (geometric mean) slower than the fastest, 1.7 % of the problems lose more than 10 %.  Fitted
+// the shapes that come near the fastest; an added constant for the launch (1.8) is left out, being the same for all.  (Inside a
+// layer, at the clock that a whole pass settles at, the same launches take up to a fifth longer.)  Median error 7 %; the shape taken is 0.5 % (geometric mean) slower than the fastest, 1.7 % of the problems lose more than 10 %.  Fitted
 // without 342 of the problems, the choice loses 0.9 % on these.  (A table fitted to M up to 4096 without a column for the residual,
 // with one entry set by hand, and blind to the split tail, lost 3.0 % on all and 3.4 % on these: 4096 x 1152 residual outputs, K =
 // 1152, 23.4 us where 128x128 tiles take 20.0; K = 4352, 51.6 where 192x128 take 46.4.)
