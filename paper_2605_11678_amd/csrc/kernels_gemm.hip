@@ -110,7 +110,7 @@ struct Stages {
 // staged through registers: 36 us for the 100 MB of 4096 x 12288 at 19 rows; now 24); the rows of A come through the same
 // ~40 bytes per clock and compute unit as the weights, hence BM = 16, 32 or 64 by the number of rows.  8B gate/up, 19 rows:
 // 76 us (128x128 register-staged kernel) -> 39, against 32 for its weights at the rate of a streaming read.
-// EPI_QKV_POST: a tile of q or k columns takes BN / 2 columns and their rotary partners dh / 2 further on, rounds them like a
+// EPI_QKV_POST: a tile of q or k columns takes BN / 2 columns and their rotary partners dh / 2 further on, scales and rounds them like a
 // plain product's, rotates and scatters them (a layer over 19 rows and 3072 cached: 122.2 us with the separate launch, now 119.8).
 // Rows past M repeat row M - 1 and are not stored.  Needs K % 64 == 0, N % 16 == 0, 16-byte aligned rows.
 struct NoPost {};
@@ -930,8 +930,9 @@ void launch_fast(const GemmArgs& a, hipStream_t st) {
 // k-tile with all compute units busy, in us.  The constants are one fit to the times of every shape on 810 problems (M 66 .. 16384
 // against 36 outputs of 256 .. 24576 columns and reductions of 256 .. 12288, weights cold, as launches in a row), weighted to
 // the shapes that come near the fastest; an added constant for the launch (1.8) is left out, being the same for all.  (Inside a
-// layer, at the clock that a whole pass settles at, the same launches take up to a fifth longer.)  Median error 7 %; the shape taken is 0.5 % (geometric mean) slower than the fastest, 1.7 % of the problems lose more than 10 %.  Fitted
-// without 342 of the problems, the choice loses 0.9 % on these.  (A table fitted to M up to 4096 without a column for the residual,
+// layer, at the clock that a whole pass settles at, the same launches take up to a fifth longer.)  Median error 7 %; the shape
+// taken is 0.5 % (geometric mean) slower than the fastest, 1.7 % of the problems lose more than 10 %.  Fitted without 342 of
+// the problems, the choice loses 0.9 % on these.  (A table fitted to M up to 4096 without a column for the residual,
 // with one entry set by hand, and blind to the split tail, lost 3.0 % on all and 3.4 % on these: 4096 x 1152 residual outputs, K =
 // 1152, 23.4 us where 128x128 tiles take 20.0; K = 4352, 51.6 where 192x128 take 46.4.)
 // What separates the shapes: a compute unit takes in about 40 bytes per clock through the global -> LDS path whatever the tile,
