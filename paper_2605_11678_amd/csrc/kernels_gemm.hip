@@ -10,13 +10,15 @@
 //    each owns a (BM/2)x(BN/2) tile, up to 4x4 MFMA tiles = 256 fp32 accumulators per lane) or stacked 4x1 (WM = 4);
 //    one workgroup per CU, two for 128x192 and 128x128 on two stages.  k-tile 64: a row of a tile is
 //    one 128-byte cache line.  Tiles go global -> LDS directly (buffer_load_dwordx4 ... lds, no staging registers) into
-//    NS = 2 .. 8 LDS stages (more for smaller tiles) that are separate arrays, so the compiler can tell
-//    the stage being filled from the one being read; the wait for a copy is an explicit s_waitcnt.  LDS rows are
+//    NS = 2 .. 8 LDS stages (more for smaller tiles; A of 192x256 and 256x192 has four and three) that are separate arrays, so the
+//    compiler can tell the stage being filled from the one being read; the wait for a copy is an explicit s_waitcnt.  LDS rows are
 //    128 bytes, unpadded (a wavefront's copy fills 1 KB = 8 rows contiguously); the 16-byte chunk index is
 //    XOR-swizzled with (row/2)%8 on both sides, which keeps the b128 fragment reads conflict-free.  Per k-tile four
 //    phases of up to 16 MFMAs, each interleaved with the fragment reads of the next phase through
-//    sched_group_barrier, ONE bare s_barrier, and the copy of the k-tile NS ahead spread over the two phases that
-//    follow the barrier (a whole k-tile of time to land).
+//    sched_group_barrier, ONE bare s_barrier, and the copies of k-tiles up to NS ahead spread over the phases that follow it.
+//    What bounds it: the copies (a loop of nothing else takes 80 us of the 102 for 4096^3 on 256x256 tiles, 137 of 148 on
+//    128x128).  They come in at about 60 bytes per ns and compute unit where lines miss the L2, at twice that where they hit
+//    (every k-tile among the first eight: 128x128 148 -> 121 us); tiles that share lines ask for them at the same time.
 //  * gemm_generic<EPI> — any shape (K % 8 == 0): 128x128 tile, 64x64 per wavefront, staged through registers.
 //  * gemm_few_rows<BM,BN,NS,EPI> — M <= 64: BN output columns per workgroup, reduction split over its 4 wavefronts.
 //
@@ -88,17 +90,17 @@ template <int NS>
 struct Stages {
     bf16_t* s[NS];
 };
-#define DL_STAGE(i, ELEMS) __shared__ __attribute__((aligned(1024))) bf16_t stage##i[ELEMS]
-#define DL_STAGES(NS, ELEMS)                                                                       \
-    Stages<NS> st{{}};                                                                            \
-    if constexpr (NS > 0) { DL_STAGE(0, ELEMS); st.s[0] = stage0; }                                      \
-    if constexpr (NS > 1) { DL_STAGE(1, ELEMS); st.s[1] = stage1; }                                      \
-    if constexpr (NS > 2) { DL_STAGE(2, ELEMS); st.s[2] = stage2; }                                      \
-    if constexpr (NS > 3) { DL_STAGE(3, ELEMS); st.s[3] = stage3; }                                      \
-    if constexpr (NS > 4) { DL_STAGE(4, ELEMS); st.s[4] = stage4; }                                      \
-    if constexpr (NS > 5) { DL_STAGE(5, ELEMS); st.s[5] = stage5; }                                      \
-    if constexpr (NS > 6) { DL_STAGE(6, ELEMS); st.s[6] = stage6; }                                      \
-    if constexpr (NS > 7) { DL_STAGE(7, ELEMS); st.s[7] = stage7; }
+#define DL_STAGE(X, i, ELEMS) __shared__ __attribute__((aligned(1024))) bf16_t X##_##i[ELEMS]
+#define DL_STAGES(X, NS, ELEMS)                                                                    \
+    Stages<NS> X{{}};                                                                             \
+    if constexpr (NS > 0) { DL_STAGE(X, 0, ELEMS); X.s[0] = X##_0; }                                     \
+    if constexpr (NS > 1) { DL_STAGE(X, 1, ELEMS); X.s[1] = X##_1; }                                     \
+    if constexpr (NS > 2) { DL_STAGE(X, 2, ELEMS); X.s[2] = X##_2; }                                     \
+    if constexpr (NS > 3) { DL_STAGE(X, 3, ELEMS); X.s[3] = X##_3; }                                     \
+    if constexpr (NS > 4) { DL_STAGE(X, 4, ELEMS); X.s[4] = X##_4; }                                     \
+    if constexpr (NS > 5) { DL_STAGE(X, 5, ELEMS); X.s[5] = X##_5; }                                     \
+    if constexpr (NS > 6) { DL_STAGE(X, 6, ELEMS); X.s[6] = X##_6; }                                     \
+    if constexpr (NS > 7) { DL_STAGE(X, 7, ELEMS); X.s[7] = X##_7; }
 
 // ---- few rows (M <= 64): one pass over the weights, bound by how many of their bytes are on the way at a time.  A 256-thread
 // workgroup owns BN output columns (for SwiGLU BN / 2 gate columns and the BN / 2 up columns that go with them) and all
@@ -121,7 +123,7 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
     constexpr int W = 4, STG = (BM + BN) * 64;           // wavefronts; elements of one wavefront's stage
     constexpr int JA = BM / 8, JB = BN / 8, TM = BM / 16, TN = BN / 16;
     typedef __attribute__((ext_vector_type(4))) float f32x4;
-    DL_STAGES(NS, W * STG)
+    DL_STAGES(st, NS, W * STG)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nk = p.K >> 6;
     const int n_my = (nk - wave + W - 1) / W;            // k-tiles wave, wave + W, ... (0 when there are fewer than wavefronts)
@@ -685,11 +687,11 @@ struct SchedEven {
     }
 };
 
-// One output tile with its top-left corner at (m0, n0).  st: NS LDS stages of at least (BM + BN) * 64 elements each.
+// One output tile with its top-left corner at (m0, n0).  sa, sb: SA >= SB LDS stages of at least BM * 64 and BN * 64 elements.
 // The four wavefronts form a WM x (4 / WM) grid.  TR: the tile's columns go to p.vt; the operands of every MFMA change places
 // (both have the same layout), which transposes the accumulators and leaves the sums as they are.
-template <int BM, int BN, int EPI, int WM, int NS, bool TR>
-__device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0, Stages<NS> st) {
+template <int BM, int BN, int EPI, int WM, int SA, int SB, bool TR>
+__device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0, Stages<SA> sa, Stages<SB> sb) {
     constexpr int BK = 64, WN = 4 / WM;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int JA = BM / 32, JB = BN / 32;            // 1 KB copy blocks (8 rows x 128 B) per wavefront and k-tile
@@ -713,22 +715,27 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     // (L%8) ^ ((row/2)%8): a b128 fragment read serves 16 lanes (16 consecutive rows, 256 bytes of banks) at a time,
     // two rows fill the 64 banks once, so the swizzle has to differ between the 8 row PAIRS (with row%8 the counters
     // showed every second LDS cycle of the kernel as a bank conflict).  Rows past the matrix edge are clamped: they produce values that the epilogue never stores.
+    // Tiles in one row of tiles start at different blocks of their rows of A, tiles in one column at different blocks of B:
+    // those that run on an XCD at the same time then ask its L2 for a line one after the other, and all but the first find it there.
+    const int rotA = n0 / BN * ((JA + 3) / 4) % JA, rotB = m0 / BM * ((JB + 3) / 4) % JB;
     uint32_t offA[JA], offB[JB];
+    int blkA[JA], blkB[JB];
 #pragma unroll
     for (int j = 0; j < JA; ++j) {
-        const int row = 8 * (wave + 4 * j) + (lane >> 3), lc = (lane & 7) ^ ((row >> 1) & 7);
+        blkA[j] = wave + 4 * (j + rotA < JA ? j + rotA : j + rotA - JA);
+        const int row = 8 * blkA[j] + (lane >> 3), lc = (lane & 7) ^ ((row >> 1) & 7);
         offA[j] = uint32_t((size_t(min(m0 + row, p.M - 1)) * p.lda + lc * 8) * 2);
     }
 #pragma unroll
     for (int j = 0; j < JB; ++j) {
-        const int row = 8 * (wave + 4 * j) + (lane >> 3), lc = (lane & 7) ^ ((row >> 1) & 7);
+        blkB[j] = wave + 4 * (j + rotB < JB ? j + rotB : j + rotB - JB);
+        const int row = 8 * blkB[j] + (lane >> 3), lc = (lane & 7) ^ ((row >> 1) & 7);
         offB[j] = uint32_t((size_t(min(n0 + row, p.N - 1)) * p.ldb + lc * 8) * 2);
     }
     // the host only takes this path for operands below 4 GB
-    const __amdgpu_buffer_rsrc_t gA = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(p.A), 0, int(uint32_t(size_t(p.M) * p.lda * 2)), kBufferFlags);
-    const __amdgpu_buffer_rsrc_t gB = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(p.B), 0, int(uint32_t(size_t(p.N) * p.ldb * 2)), kBufferFlags);
+    const int sizeA = int(uint32_t(size_t(p.M) * p.lda * 2)), sizeB = int(uint32_t(size_t(p.N) * p.ldb * 2));
+    const __amdgpu_buffer_rsrc_t gA = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.A), 0, sizeA, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t gB = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.B), 0, sizeB, kBufferFlags);
     // fragment read offsets (elements) inside a stage, one per 16-wide k step
     const int lr = lane & 31, g2 = lane >> 5;
     int rdA[4], rdB[4];
@@ -736,23 +743,29 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     for (int kk = 0; kk < 4; ++kk) {
         const int pc = (2 * kk + g2) ^ ((lr >> 1) & 7);
         rdA[kk] = ((BM / WM) * wm + lr) * BK + pc * 8;
-        rdB[kk] = BM * BK + ((BN / WN) * wn + lr) * BK + pc * 8;
+        rdB[kk] = ((BN / WN) * wn + lr) * BK + pc * 8;
     }
 
     bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
-    auto copyA = [&](bf16_t* S, int kt) {
+    const int nk = p.K / BK;                             // host guarantees K % 128 == 0: nk is even and >= 2
+    // copies j0 .. j1 - 1 of a k-tile of A or B
+    constexpr bool EXITS = SA != SB;
+    const int endA = sizeA < 0 ? (nk - 1) * (BK * 2) : sizeA, endB = sizeB < 0 ? (nk - 1) * (BK * 2) : sizeB;
+    auto copyA = [&](bf16_t* S, int kt, int j0, int j1) {
+        const int so = !EXITS || kt < nk ? kt * (BK * 2) : endA;
 #pragma unroll
-        for (int j = 0; j < JA; ++j) DL_BLL16(gA, offA[j], kt * (BK * 2), S + (wave + 4 * j) * 512);
+        for (int j = j0; j < j1; ++j) DL_BLL16(gA, offA[j], so, S + blkA[j] * 512);
     };
-    auto copyB = [&](bf16_t* S, int kt) {
+    auto copyB = [&](bf16_t* S, int kt, int j0, int j1) {
+        const int so = !EXITS || kt < nk ? kt * (BK * 2) : endB;
 #pragma unroll
-        for (int j = 0; j < JB; ++j) DL_BLL16(gB, offB[j], kt * (BK * 2), S + BM * BK + (wave + 4 * j) * 512);
+        for (int j = j0; j < j1; ++j) DL_BLL16(gB, offB[j], so, S + blkB[j] * 512);
     };
-    auto ldfrag = [&](bf16x8* a, bf16x8* b, const bf16_t* S, int kk) {
+    auto ldfrag = [&](bf16x8* a, bf16x8* b, const bf16_t* S, const bf16_t* R, int kk) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const bf16x8*>(S + rdA[kk] + 32 * i * BK);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const bf16x8*>(S + rdB[kk] + 32 * j * BK);
+        for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const bf16x8*>(R + rdB[kk] + 32 * j * BK);
     };
     // serpentine order over the accumulator tiles: from one MFMA to the next exactly one operand changes
     auto mma = [&](const bf16x8* a, const bf16x8* b) {
@@ -770,78 +783,104 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    const int nk = p.K / BK;                             // host guarantees K % 128 == 0: nk is even and >= 2
-
     // One k-tile = four phases of TM*TN MFMAs (16-wide k steps), each overlapped with the fragment reads of the next
     // phase.  Before the last phase the wavefront waits for its own copies of k-tile kt+1 and for all of its LDS reads
     // and meets the others at the one barrier of the k-tile; past it (a) k-tile kt+1 has landed for everyone and
-    // (b) nobody reads stage kt any more, so the copy of k-tile kt+NS into that stage starts right there: its A half
-    // is spread over the last phase, its B half over the first phase of the next k-tile.  With NS = 2 stages a copy has
-    // one k-tile of MFMAs to land (64 per wavefront for the large tiles: enough); a smaller tile's k-tile is 4 to 36 MFMAs a
-    // wavefront, so it runs three to eight stages and its copies have two to seven k-tiles.
-    // REM = k-tiles after this one, capped at NS (the steady state): with fewer than NS - 1 left the copy's B half has
-    // nothing to fetch, with fewer than NS its A half; the wait leaves the copies younger than k-tile kt+1 in flight.
-    auto ktile = [&](bf16_t* cur, bf16_t* nxt, bf16_t* prv, int kt, auto rem_c) {
-        constexpr int REM = decltype(rem_c)::value;
-        constexpr bool kB = REM >= NS - 1, kA = REM >= NS;
-        ldfrag(a1, b1, cur, 1);
-        if (kB) copyB(prv, kt + NS - 1);                 // second half of the copy begun in the previous k-tile
+    // (b) nobody reads the stages of kt any more, so the copies into them start right there: B of kt+SB in the last phase and the
+    // first of the next k-tile, A of kt+SA in the two that follow.  Four phases with a quarter of the copies each: a wavefront
+    // that issues more at a time waits in front of the copy path, and its MFMAs with it (256 x 128 wavefront pairs, 128x256 on three:
+    // 4096^3 116.5 -> 111.6 us, 4096 x 1152, K = 4352: 48.0 -> 44.8).  On two stages there is no time for that, a copy has to land
+    // within a k-tile: B goes with the last phase, A with the first.
+    // 192x256 and 256x192 have two stages of the operand with more to copy and four or three of the other: half of the copies get a
+    // k-tile or two more to land (192x256: 3072 x 4096, K = 12288, 238 -> 220 us; 3072 x 6144, K = 4096, 156 -> 137).
+    // REM = k-tiles after this one, capped at SA (the steady state): with too few left a copy has nothing to fetch; the wait
+    // leaves the copies younger than k-tile kt+1 in flight.
+    constexpr bool SPREAD = SA > 2;
+    constexpr int B0 = SPREAD ? JB / 2 : JB, A0 = SPREAD ? 0 : JA, A1 = SPREAD ? JA / 2 : JA;
+    constexpr int U = SA % SB == 0 ? SA : SA * SB;       // k-tiles until the stages come round
+    auto ktile = [&](auto i_c, int kt, auto rem_c) {
+        constexpr int I = decltype(i_c)::value, REM = decltype(rem_c)::value;
+        constexpr bool kB = REM >= SB, kB1 = REM >= SB - 1, kA = REM >= SA - 1;
+        bf16_t *ca = sa.s[I % SA], *cb = sb.s[I % SB], *pa = sa.s[(I + SA - 1) % SA], *pb = sb.s[(I + SB - 1) % SB];
+        ldfrag(a1, b1, ca, cb, 1);
+        if (kB1) copyB(pb, kt + SB - 1, B0, JB);
+        if (kA) copyA(pa, kt + SA - 1, 0, A0);
         mma(a0, b0);
-        interleave(std::integral_constant<int, (kB ? JB : 0)>{});
-        ldfrag(a0, b0, cur, 2);
+        interleave(std::integral_constant<int, (kB1 ? JB - B0 : 0) + (kA ? A0 : 0)>{});
+        ldfrag(a0, b0, ca, cb, 2);
+        if (kA) copyA(pa, kt + SA - 1, A0, A1);
         mma(a1, b1);
-        interleave(std::integral_constant<int, 0>{});
-        ldfrag(a1, b1, cur, 3);
+        interleave(std::integral_constant<int, (kA ? A1 - A0 : 0)>{});
+        ldfrag(a1, b1, ca, cb, 3);
+        if (kA) copyA(pa, kt + SA - 1, A1, JA);
         mma(a0, b0);
-        interleave(std::integral_constant<int, 0>{});
+        interleave(std::integral_constant<int, (kA ? JA - A1 : 0)>{});
         if constexpr (REM >= 1) {
-            constexpr int younger = (REM - 1 < NS - 2 ? REM - 1 : NS - 2) * (JA + JB);
-            DL_WAIT_VM_LGKM0(younger);
+            // younger than k-tile kt+1's last copy: B of kt+2 .. kt+SB-1 and A of kt+2 (SA > SB: kt+1+SA-SB) .. kt+SA-1
+            constexpr int nB = (REM - 1 < SB - 2 ? REM - 1 : SB - 2);
+            constexpr int lo = SA > SB ? 1 + SA - SB : 2, hi = SA - 1 < REM ? SA - 1 : REM;
+            DL_WAIT_VM_LGKM0((nB > 0 ? nB : 0) * JB + (hi >= lo ? hi - lo + 1 : 0) * JA);
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            ldfrag(a0, b0, nxt, 0);
-            if (kA) copyA(cur, kt + NS);
+            ldfrag(a0, b0, sa.s[(I + 1) % SA], sb.s[(I + 1) % SB], 0);
+            if (kB) copyB(cb, kt + SB, 0, B0);
             mma(a1, b1);
-            interleave(std::integral_constant<int, (kA ? JA : 0)>{});
+            interleave(std::integral_constant<int, (kB ? B0 : 0)>{});
         } else {
             mma(a1, b1);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // k-tiles kt .. kt + N - 1, of which the last has `AFTER` k-tiles behind it; k-tile kt sits in stage 0
-    auto run = [&](auto self, int kt, auto i_c, auto n_c, auto after_c) {
-        constexpr int I = decltype(i_c)::value, N = decltype(n_c)::value, AFTER = decltype(after_c)::value;
-        constexpr int REM = N - 1 - I + AFTER < NS ? N - 1 - I + AFTER : NS;
-        ktile(st.s[I % NS], st.s[(I + 1) % NS], st.s[(I + NS - 1) % NS], kt + I, std::integral_constant<int, REM>{});
-        if constexpr (I + 1 < N) self(self, kt, std::integral_constant<int, I + 1>{}, n_c, after_c);
-    };
     using std::integral_constant;
-    // the first NS k-tiles, of which the last comes without its B half (that is copied during k-tile 0)
+    // the first copies in the order of the main loop, up to what the last phase of a k-tile -1 would have issued
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        copyA(st.s[s], s);
-        if (s + 1 < NS) copyB(st.s[s], s);
+    for (int s = 0; s < SA; ++s) {
+        const int kb = s - (SA - SB);
+        if (kb >= 0) copyB(sb.s[kb], kb, 0, s + 1 < SA ? JB : B0);
+        if (s + 1 < SA) copyA(sa.s[s], s, 0, JA);
     }
-    DL_WAIT_VM((NS - 2) * (JA + JB) + JA);               // k-tile 0 has landed (this wavefront's share)
+    // k-tile 0 has landed (this wavefront's share): behind B of k-tile 0 come A of SA - SB (SA == SB: 1) .. SA - 2 and B of 1 .. SB - 1
+    DL_WAIT_VM((SA == SB ? SB - 2 : SB - 1) * JA + (SB - 2) * JB + B0);
     __builtin_amdgcn_s_barrier();
-    ldfrag(a0, b0, st.s[0], 0);
+    ldfrag(a0, b0, sa.s[0], sb.s[0], 0);
     __builtin_amdgcn_sched_barrier(0);
-    int kt = 0;
-    for (; kt + 2 * NS <= nk; kt += NS)                  // whole turns of the stages in the steady state
-        run(run, kt, integral_constant<int, 0>{}, integral_constant<int, NS>{}, integral_constant<int, NS>{});
-    // NS .. 2 NS - 1 are left (the host takes a tile only for nk >= NS; nk is even, so with an even NS the rest is too)
-    auto rest = [&](auto self, auto n_c) {
-        constexpr int N = decltype(n_c)::value;
-        if constexpr (N < 2 * NS) {
-            if ((NS % 2 == 1 || N % 2 == 0) && nk - kt == N) {
-                run(run, kt, integral_constant<int, 0>{}, n_c, integral_constant<int, 0>{});
-                DL_MFMA_SETTLE();
-            } else {
-                self(self, integral_constant<int, N + 1>{});
+    if constexpr (EXITS) {
+        // every k-tile like one of the steady state, left behind the last one: its copies lie past the end of their buffer and
+        // fetch nothing (2 GB and more: fetch the last k-tile again).  Code for every remainder, as below, spilled accumulators here.
+        auto turn = [&](auto self, int kt, auto i_c) -> bool {
+            constexpr int I = decltype(i_c)::value;
+            ktile(i_c, kt + I, integral_constant<int, SA>{});
+            if (I % 2 == 1 && kt + I + 1 == nk) return true;
+            if constexpr (I + 1 < U) return self(self, kt, integral_constant<int, I + 1>{});
+            return false;
+        };
+        for (int kt = 0; !turn(turn, kt, integral_constant<int, 0>{}); kt += U) {}
+        DL_MFMA_SETTLE();
+        DL_WAIT_VM(0);                                   // nothing is on its way into the LDS when the workgroup ends
+    } else {
+        // k-tiles kt .. kt + N - 1, of which the last has `AFTER` k-tiles behind it; k-tile kt sits in stage 0
+        auto run = [&](auto self, int kt, auto i_c, auto n_c, auto after_c) {
+            constexpr int I = decltype(i_c)::value, N = decltype(n_c)::value, AFTER = decltype(after_c)::value;
+            ktile(i_c, kt + I, integral_constant<int, (N - 1 - I + AFTER < SA ? N - 1 - I + AFTER : SA)>{});
+            if constexpr (I + 1 < N) self(self, kt, integral_constant<int, I + 1>{}, n_c, after_c);
+        };
+        int kt = 0;
+        for (; kt + 2 * SA <= nk; kt += SA)              // whole turns of the stages in the steady state
+            run(run, kt, integral_constant<int, 0>{}, integral_constant<int, SA>{}, integral_constant<int, SA>{});
+        // SA .. 2 SA - 1 are left (the host takes a tile only for nk >= SA; nk is even, so with an even SA the rest is too)
+        auto rest = [&](auto self, auto n_c) {
+            constexpr int N = decltype(n_c)::value;
+            if constexpr (N < 2 * SA) {
+                if ((SA % 2 == 1 || N % 2 == 0) && nk - kt == N) {
+                    run(run, kt, integral_constant<int, 0>{}, n_c, integral_constant<int, 0>{});
+                    DL_MFMA_SETTLE();
+                } else {
+                    self(self, integral_constant<int, N + 1>{});
+                }
             }
-        }
-    };
-    rest(rest, integral_constant<int, NS>{});
+        };
+        rest(rest, integral_constant<int, SA>{});
+    }
 
     const int mw = m0 + (BM / WM) * wm, nw = n0 + (BN / WN) * wn;
     const int n_end = min(p.N, n0 + BN);
@@ -865,27 +904,30 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
 // 3.5 us at 731 x 3456 (the product 12.6, now 12.4 with its V^T columns), 6.0 at 4096 x 3456 (33.8, now 36.0), 5.2 at 3072 x
 // 2048 (45.4, now 46.6).  With a predicate and a 64-bit address per element, as the other epilogues had, this one took more
 // than the launch it replaces (4096 x 3456: 45.6).
-template <int BM, int BN, int EPI, int WM = 2, int NS = 2>
-__device__ __forceinline__ void fast_tile(const GemmArgs& p, int m0, int n0, Stages<NS> st) {
+template <int BM, int BN, int EPI, int WM, int SA, int SB>
+__device__ __forceinline__ void fast_tile(const GemmArgs& p, int m0, int n0, Stages<SA> sa, Stages<SB> sb) {
     if constexpr (EPI == EPI_BF16) {
         if (n0 >= first_vt_col(p) && p.vt_ld < (1 << 23)) {      // (32-bit offsets inside a wavefront tile)
-            fast_tile_any<BM, BN, EPI, WM, NS, true>(p, m0, n0, st);
+            fast_tile_any<BM, BN, EPI, WM, SA, SB, true>(p, m0, n0, sa, sb);
             return;
         }
     }
-    fast_tile_any<BM, BN, EPI, WM, NS, false>(p, m0, n0, st);
+    fast_tile_any<BM, BN, EPI, WM, SA, SB, false>(p, m0, n0, sa, sb);
 }
 
 // Two-stage tiles of at most 128x192 leave room for two workgroups per compute unit (at most 80 KB of LDS and 128
 // accumulators each): one's prologue and epilogue hide under the other's main loop.
 constexpr bool two_per_cu(int bm, int bn, int ns) { return bm == 128 && bn <= 192 && ns == 2; }
-template <int BM, int BN, int EPI, int WM = 2, int NS = 2>
+// stages of A: all of the LDS where B has two
+constexpr int stages_a(int bm, int bn, int ns) { return bm == 192 && bn == 256 ? 4 : (bm == 256 && bn == 192 ? 3 : ns); }
+template <int BM, int BN, int EPI, int WM, int NS>
 __global__ __launch_bounds__(256, two_per_cu(BM, BN, NS) ? 2 : 1) void gemm_fast(GemmArgs p) {
-    DL_STAGES(NS, (BM + BN) * 64)
+    DL_STAGES(sa, stages_a(BM, BN, NS), BM * 64)
+    DL_STAGES(sb, NS, BN * 64)
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
     int tm, tn;
     if (!tile_of(blockIdx.x, tiles_m, tiles_n, &tm, &tn)) return;
-    fast_tile<BM, BN, EPI, WM, NS>(p, tm * BM, tn * BN, st);
+    fast_tile<BM, BN, EPI, WM, stages_a(BM, BN, NS), NS>(p, tm * BM, tn * BN, sa, sb);
 }
 
 // 256x256 tiles whose count is r full rounds of 256 workgroups plus a remainder of at most half a round: the last
@@ -894,24 +936,25 @@ __global__ __launch_bounds__(256, two_per_cu(BM, BN, NS) ? 2 : 1) void gemm_fast
 // Block b < n_big computes whole tile b (in the XCD-aware order), block n_big + 2 j + h half h of tile n_big + j.
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_fast_split_tail(GemmArgs p, int n_big) {
-    DL_STAGES(2, 512 * 64)
+    DL_STAGES(sa, 2, 256 * 64)
+    DL_STAGES(sb, 2, 256 * 64)
     const int tiles_m = (p.M + 255) / 256, tiles_n = (p.N + 255) / 256;
     const int b = blockIdx.x;
     const int v = b < n_big ? b : n_big + ((b - n_big) >> 1);
     int tm, tn;
     if (!tile_of(v, tiles_m, tiles_n, &tm, &tn)) return;
     if (b < n_big) {
-        fast_tile<256, 256, EPI>(p, tm * 256, tn * 256, st);
+        fast_tile<256, 256, EPI, 2, 2, 2>(p, tm * 256, tn * 256, sa, sb);
     } else {
         const int m0 = tm * 256 + 128 * ((b - n_big) & 1);
-        if (m0 < p.M) fast_tile<128, 256, EPI>(p, m0, tn * 256, st);
+        if (m0 < p.M) fast_tile<128, 256, EPI, 2, 2, 2>(p, m0, tn * 256, sa, sb);
     }
 }
 
 // tile_of deals tiles to 8 XCDs in equal shares: the split needs every virtual index below `tiles` to be valid
 constexpr bool splits_tail(long tiles) { return tiles > 256 && tiles % 8 == 0 && tiles % 256 > 0 && tiles % 256 <= 128; }
 
-template <int BM, int BN, int EPI, int WM = 2, int NS = 2>
+template <int BM, int BN, int EPI, int WM, int NS>
 void launch_fast(const GemmArgs& a, hipStream_t st) {
     const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
     if (BM == 256 && BN == 256) {
@@ -932,7 +975,9 @@ void launch_fast(const GemmArgs& a, hipStream_t st) {
 // the shapes that come near the fastest; an added constant for the launch (1.8) is left out, being the same for all.  (Inside a
 // layer, at the clock that a whole pass settles at, the same launches take up to a fifth longer.)  Median error 7 %; the shape
 // taken is 0.5 % (geometric mean) slower than the fastest, 1.7 % of the problems lose more than 10 %.  Fitted without 342 of
-// the problems, the choice loses 0.9 % on these.  (A table fitted to M up to 4096 without a column for the residual,
+// the problems, the choice loses 0.9 % on these.  (Since the copies are spread and rotated every shape but 256x256 is 1 to 8 % faster,
+// 192x256 and 256x192 most; on the times measured then, which the test holds, the same table loses 0.6 % and 1.6 % of the problems more than
+// 10 %, a new fit of these two rows 0.55 %.)  (A table fitted to M up to 4096 without a column for the residual,
 // with one entry set by hand, and blind to the split tail, lost 3.0 % on all and 3.4 % on these: 4096 x 1152 residual outputs, K =
 // 1152, 23.4 us where 128x128 tiles take 20.0; K = 4352, 51.6 where 192x128 take 46.4.)
 // What separates the shapes: a compute unit takes in about 40 bytes per clock through the global -> LDS path whatever the tile,
