@@ -25,6 +25,8 @@
 // starts from minus the softmax's reference maximum, so the base-2 exponential takes the accumulator as it is: with the scale
 // and the reference in an FMA in front of every exponential, 3072 tokens of the 8B shape took 96 us, now 90.  Masking is skipped on tiles that cannot need it, and the
 // reference moves lazily (only past a 2^8 margin), so the running output is rescaled about once.
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace dlk {
@@ -368,6 +370,246 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs p, int tps) {
         }
 }
 
+// Few queries over many keys: a workgroup is one head and 32 queries, its four wavefronts take the K/V tiles in turn, each through
+// LDS stages of its own (one K, one V^T tile: the next K tile is copied while the probabilities are made, the next V^T tile during
+// the score product), so nothing waits for another wavefront until the four partial results meet in LDS.  Bound by the latency of a
+// tile's copies and by the chain of products and exponentials, hence as many wavefronts as there are tiles rather than few that
+// share a tile between heads.  RUNS: the launch's z dimension divides the tiles once more, see attn_merge_kernel.
+// Heads of a KV head sit Hkv workgroups apart, with 8 KV heads on one XCD: its L2 holds their K and V once.
+template <int DK, int DV, bool RUNS, bool ONES>
+__global__ __launch_bounds__(256, 1) void attn_keys_kernel(AttnArgs p, int tps) {
+    constexpr int KCPR = DK / 8, NK = KCPR, NV = DV / 8;   // copy instructions of a K and a V^T tile
+    __shared__ __attribute__((aligned(1024))) bf16_t sK[4][BKV * DK];
+    __shared__ __attribute__((aligned(1024))) bf16_t sV[4][DV * BKV];
+    __shared__ float s_ml[4][2][32];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lq = lane & 31, g2 = lane >> 5;
+    const int krow = (lq & 0x13) | ((lq & 4) << 1) | ((lq & 8) >> 1);
+    const int group = p.Hq / p.Hkv, kvh = blockIdx.x % p.Hkv, h = kvh * group + blockIdx.x / p.Hkv;
+    const int q0 = blockIdx.y * 32, tq = q0 + lq, qpos = p.q_pos0 + tq;
+    const int kv_end = p.causal ? min(p.S, p.q_pos0 + min(q0 + 32, p.T)) : p.S;
+    const int nt_all = (kv_end + BKV - 1) / BKV;
+    const int t_begin = RUNS ? int(blockIdx.z) * tps : 0, nt = RUNS ? min(nt_all, t_begin + tps) : nt_all;
+    const int k_size = int(uint32_t(size_t(p.S) * p.ldk * 2)), v_size = int(uint32_t(size_t(p.dh) * p.ldv * 2));
+    const __amdgpu_buffer_rsrc_t kbuf = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(p.k + size_t(kvh) * p.k_head_stride), 0, k_size, kAttnBufferFlags);
+    const __amdgpu_buffer_rsrc_t vbuf = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(p.vt + size_t(kvh) * p.v_head_stride), 0, v_size, kAttnBufferFlags);
+    // offsets, swizzles, clamps and the row of ones as in attn_kernel
+    uint32_t koff[NK], voff[NV];
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+        const int id = 64 * i + lane, row = id / KCPR, c = (id % KCPR) ^ chunk_swizzle<KCPR>(row);
+        koff[i] = uint32_t((size_t(row) * p.ldk + (8 * c < p.dh ? 8 * c : 0)) * 2);
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int row = 8 * i + (lane >> 3), c = (lane & 7) ^ chunk_swizzle<8>(row);
+        voff[i] = uint32_t((size_t(min(row, p.dh - 1)) * p.ldv + 8 * c) * 2);
+    }
+    bf16_t *cK = sK[wave], *cV = sV[wave];
+    // always as many copies, so that the waits below count the same ones everywhere: for a tile that is not there (the wavefront's
+    // last turn) they lie past the end of the buffer and fetch nothing
+    auto copyK = [&](int t) {
+        const int so = t < nt ? t * (BKV * 2) * p.ldk : k_size;
+#pragma unroll
+        for (int i = 0; i < NK; ++i) DL_ATT_BLL16(kbuf, koff[i], so, cK + 512 * i);
+    };
+    auto copyV = [&](int t) {
+        const int so = t < nt ? t * (BKV * 2) : v_size;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (ONES && i == NV - 1) {
+                if (lane < 56) DL_ATT_BLL16(vbuf, voff[i], so, cV + 512 * i);
+            } else {
+                DL_ATT_BLL16(vbuf, voff[i], so, cV + 512 * i);
+            }
+        }
+    };
+    if (ONES && lane < 8) {
+        const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+        *reinterpret_cast<u32x4*>(cV + (DV - 1) * BKV + 8 * lane) = ones;
+    }
+    int t = t_begin + wave;
+    u32x4 qv[DK / 16];
+    {
+        const bf16_t* qrow = p.q + size_t(min(tq, p.T - 1)) * p.ldq + size_t(h) * p.dh;
+#pragma unroll
+        for (int kk = 0; kk < DK / 16; ++kk) {
+            const int e = 16 * kk + 8 * g2;
+            qv[kk] = *reinterpret_cast<const u32x4*>(qrow + (e < p.dh ? e : 0));
+        }
+    }
+    copyK(t);
+    copyV(t);
+    bf16x8 qf[DK / 16];
+#pragma unroll
+    for (int kk = 0; kk < DK / 16; ++kk) {
+        const int e = 16 * kk + 8 * g2;
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        u32x4 v = (tq < p.T && e < p.dh) ? qv[kk] : z;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {                      // (vector instructions' results: no wait for later copies in the loop)
+            uint32_t y;
+            asm volatile("v_mov_b32 %0, %1" : "=v"(y) : "v"(v[w]));
+            v[w] = y;
+        }
+        qf[kk] = *reinterpret_cast<bf16x8*>(&v);
+    }
+    f32x16 accO[DV / 32], base;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        base[r] = 0.0f;
+#pragma unroll
+        for (int dt = 0; dt < DV / 32; ++dt) accO[dt][r] = 0.0f;
+    }
+    float m_ref = 0.0f, margin = -INFINITY, l_run = 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
+    for (; t < nt; t += 4) {
+        const int j0 = t * BKV;
+        // K of this tile has landed, V^T may be on its way
+        __builtin_amdgcn_s_waitcnt((NV & 0xF) | ((NV >> 4) << 14) | (0x7 << 4) | (0x0 << 8));
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 accS[2];
+        {
+            constexpr int NS = 2 * (DK / 16);
+            bf16x8 fr[NS];
+#pragma unroll
+            for (int n = 0; n < NS; ++n) {
+                const int row = 32 * (n / (DK / 16)) + krow, pc = (2 * (n % (DK / 16)) + g2) ^ chunk_swizzle<KCPR>(row);
+                fr[n] = *reinterpret_cast<const bf16x8*>(cK + row * DK + 8 * pc);
+            }
+            __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): the fragments are in registers, the stage is free
+            __builtin_amdgcn_sched_barrier(0);
+            copyK(t + 4);
+#pragma unroll
+            for (int n = 0; n < NS; ++n)
+                accS[n / (DK / 16)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n], qf[n % (DK / 16)],
+                                                                              n % (DK / 16) == 0 ? base : accS[n / (DK / 16)], 0, 0, 0);
+        }
+        if ((j0 + BKV > p.S) || (p.causal && j0 + BKV - 1 > p.q_pos0 + q0)) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int kv = j0 + 32 * i + 16 * (r >> 3) + 8 * g2 + (r & 7);
+                    accS[i][r] = kv < p.S && (!p.causal || kv <= qpos) ? accS[i][r] : -INFINITY;
+                }
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, accS[i][r]);
+        {
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+        }
+        constexpr float LAZY = 8.0f;                       // (the reference maximum moves lazily, as in attn_kernel)
+        const bool move = mx > margin;
+        if (__any(move)) {
+            const float shift = move ? mx : 0.0f;
+            const float alpha = __builtin_amdgcn_exp2f(-fmaxf(shift, 0.0f));
+            l_run *= alpha;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+#pragma unroll
+                for (int dt = 0; dt < DV / 32; ++dt) accO[dt][r] *= alpha;
+                accS[0][r] -= shift;
+                accS[1][r] -= shift;
+            }
+            m_ref += shift;
+            margin = move ? LAZY : margin;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) base[r] = -m_ref;
+        }
+        float psum = 0.0f;
+        bf16x8 pf[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float pv = __builtin_amdgcn_exp2f(accS[i][8 * t2 + j]);
+                    if (!ONES) psum += pv;
+                    pf[i][t2][j] = (__bf16)pv;
+                }
+        l_run += psum;
+        // V^T has landed, the next K tile may be on its way
+        __builtin_amdgcn_s_waitcnt((NK & 0xF) | ((NK >> 4) << 14) | (0x7 << 4) | (0x0 << 8));
+        __builtin_amdgcn_sched_barrier(0);
+        {
+            constexpr int NP = (DV / 32) * 4;
+            bf16x8 fr[NP];
+#pragma unroll
+            for (int n = 0; n < NP; ++n) {
+                const int row = 32 * (n / 4) + lq, pc = (2 * (n % 4) + g2) ^ chunk_swizzle<8>(row);
+                fr[n] = *reinterpret_cast<const bf16x8*>(cV + row * BKV + 8 * pc);
+            }
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+            __builtin_amdgcn_sched_barrier(0);
+            copyV(t + 4);
+#pragma unroll
+            for (int n = 0; n < NP; ++n)
+                accO[n / 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n], pf[(n / 2) % 2][n % 2], accO[n / 4], 0, 0, 0);
+        }
+    }
+    const float l_tot = ONES ? __shfl(accO[DV / 32 - 1][15], 32 + lq, 64) : l_run + __shfl_xor(l_run, 32, 64);
+    // the wavefront's V^T stage takes its output, [feature][query]: DV * 32 floats, just its size
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_sched_barrier(0);
+    float* mine = reinterpret_cast<float*>(cV);
+#pragma unroll
+    for (int dt = 0; dt < DV / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mine[(32 * dt + 8 * (r >> 2) + 4 * g2 + (r & 3)) * 32 + lq] = accO[dt][r];
+    if (g2 == 0) {
+        s_ml[wave][0][lq] = margin == -INFINITY ? -INFINITY : m_ref;
+        s_ml[wave][1][lq] = l_tot;
+    }
+    __syncthreads();
+    // eight threads a query, DV / 8 features each; the wavefronts' results in order
+    constexpr int FE = DV / 8;
+    const int q = tid & 31, e0 = (tid >> 5) * FE;
+    if (q0 + q >= p.T) return;
+    float m = -INFINITY, l = 0.0f, wt[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) m = fmaxf(m, s_ml[w][0][q]);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        wt[w] = s_ml[w][0][q] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(s_ml[w][0][q] - m);
+        l = fmaf(wt[w], s_ml[w][1][q], l);
+    }
+    float o[FE];
+#pragma unroll
+    for (int x = 0; x < FE; ++x) {
+        o[x] = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) o[x] = fmaf(wt[w], reinterpret_cast<const float*>(sV[w])[(e0 + x) * 32 + q], o[x]);
+    }
+    if constexpr (RUNS) {
+        float* prow = p.split_ws + ((size_t(blockIdx.z) * p.Hq + h) * p.T + q0 + q) * (DV + 4);
+#pragma unroll
+        for (int x = 0; x < FE; x += 4) *reinterpret_cast<float4*>(prow + e0 + x) = make_float4(o[x], o[x + 1], o[x + 2], o[x + 3]);
+        if (e0 == 0) {
+            prow[DV] = m;
+            prow[DV + 1] = l;
+        }
+        return;
+    }
+    const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+    bf16_t* orow = p.out + size_t(q0 + q) * p.ldo + size_t(h) * p.dh;
+#pragma unroll
+    for (int x = 0; x < FE; x += 4)
+        if (e0 + x < p.dh) {
+            bf16x4 b;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) b[j] = (__bf16)(o[x + j] * inv);
+            *reinterpret_cast<bf16x4*>(orow + e0 + x) = b;
+        }
+}
+
 // out[query, head] = sum_z w_z O_z / sum_z w_z l_z with w_z = 2^(m_z - max m), runs z taken in order.  At most 16
 // runs; every run's values are requested before the first is used (index clamped to the last run, weight zero).
 template <int DHP>
@@ -398,34 +640,62 @@ __global__ __launch_bounds__(128) void attn_merge_kernel(AttnArgs p, int n_runs)
     if (e < p.dh) p.out[size_t(tq) * p.ldo + size_t(h) * p.dh + e] = f_to_bf16_attn(den > 0.0f ? num / den : 0.0f);
 }
 
-// At most 128 queries over at least 512 keys: the key range is cut over the z dimension, into runs of at least two tiles, as
-// many as give every compute unit a workgroup, at most 16, and no more than the scratch holds.  19 queries of 32 heads over
-// 3091 cached keys: 8 workgroups walked 49 tiles each in 62 us; 32 workgroups in 4 runs (what the scratch holds) and the
-// merge take 18 + 5.
-template <int DK, int DV, bool ONES>
-void launch_attn(const AttnArgs& a, hipStream_t st) {
-    const int group = a.Hq / a.Hkv;
-    const bool heads = group % 4 == 0;
-    dim3 grid = heads ? dim3(a.Hq / 4, (a.T + 31) / 32) : dim3(a.Hq, (a.T + 127) / 128);
-    const int nt = (a.S + BKV - 1) / BKV;
-    if (a.split_ws && a.T <= 128 && nt >= 8) {
-        const uint64_t fit = a.split_ws_bytes / (uint64_t(a.Hq) * a.T * (DV + 4) * 4);
-        const int want = int(256 / (grid.x * grid.y));
-        int n_runs = nt / 2 < 16 ? nt / 2 : 16;
-        if (n_runs > want) n_runs = want;
-        if (uint64_t(n_runs) > fit) n_runs = int(fit);
-        if (n_runs >= 2) {
-            const int tps = (nt + n_runs - 1) / n_runs;
-            n_runs = (nt + tps - 1) / tps;                   // every run has at least one tile
-            grid.z = n_runs;
-            if (heads) hipLaunchKernelGGL((attn_kernel<DK, DV, true, true, ONES>), grid, dim3(256), 0, st, a, tps);
-            else hipLaunchKernelGGL((attn_kernel<DK, DV, false, true, ONES>), grid, dim3(256), 0, st, a, tps);
-            hipLaunchKernelGGL(attn_merge_kernel<DV>, dim3(a.T, a.Hq), dim3(128), 0, st, a, n_runs);
-            return;
+// How a launch divides its work: queries, heads and runs of keys over workgroups, one of two kernels.  attn_kernel walks a K/V tile in
+// about a microsecond for its four heads or 128 queries; attn_keys_kernel takes about 1.8 us a tile, one head and 32 queries, but its
+// four wavefronts walk four tiles at a time, one workgroup to a compute unit.  A split into runs costs a second launch, and the
+// longer start and end of attn_keys_kernel 1.5 us.  (8B layer over 3072 cached positions, attn_kernel / attn_keys_kernel, us: 8 queries 13.9 / 13.9,
+// 19: 19.4 / 14.7, 32: 30.6 / 19.1, 64: 32.0 / 20.5, 128: 50.6 / 25.1, 200: 52.0 / 26.4; two rounds of workgroups: 500: 56.9 / 52.2, 800: 62.2 / 101;
+// encoder, 150 patches: 6.9 / 6.4, 400: 10.1 / 7.9, two rounds: 731: 14.2 / 16.4; 64 queries of the action head over 3072: 12.3 / 12.8.)
+struct AttnSplit {
+    bool keys;                                             // attn_keys_kernel
+    int runs, tps;                                         // runs of tps tiles (1: no second launch)
+};
+AttnSplit attn_split(const AttnArgs& a, int dv) {
+    const int nt = (a.S + BKV - 1) / BKV, qb = (a.T + 31) / 32;
+    const bool heads = (a.Hq / a.Hkv) % 4 == 0;
+    // runs that the scratch holds; at most 128 queries over at least 512 keys are cut, into runs of at least two tiles, at most 16
+    uint64_t fit = 1;
+    if (a.split_ws && a.T <= 128 && nt >= 8) fit = a.split_ws_bytes / (uint64_t(a.Hq) * a.T * (dv + 4) * 4);
+    int most = nt / 2 < 16 ? nt / 2 : 16;
+    if (uint64_t(most) > fit) most = int(fit);
+    if (most < 1) most = 1;
+    auto cut = [&](bool keys, int runs) {                  // (every run has at least one tile)
+        const int tps = (nt + runs - 1) / runs;
+        return AttnSplit{keys, (nt + tps - 1) / tps, tps};
+    };
+    constexpr float kMerge = 4.5f, kTile = 1.0f, kKeysTile = 1.8f, kKeysEdge = 1.5f;
+    const int wgs = heads ? a.Hq / 4 * qb : a.Hq * ((a.T + 127) / 128);
+    AttnSplit best = cut(false, std::min(most, std::max(256 / wgs, 1)));
+    float cost = kTile * float(best.tps) + (best.runs > 1 ? kMerge : 0.0f);
+    for (int r = 1; r <= most; r *= 2) {
+        const AttnSplit k = cut(true, r);
+        if (long(a.Hq) * qb * k.runs > 256) break;         // one workgroup to a compute unit: no second round
+        const float c = kKeysEdge + kKeysTile * float((k.tps + 3) / 4) + (k.runs > 1 ? kMerge : 0.0f);
+        if (c < cost) {
+            cost = c;
+            best = k;
         }
     }
-    if (heads) hipLaunchKernelGGL((attn_kernel<DK, DV, true, false, ONES>), grid, dim3(256), 0, st, a, 0);
-    else hipLaunchKernelGGL((attn_kernel<DK, DV, false, false, ONES>), grid, dim3(256), 0, st, a, 0);
+    return best;
+}
+
+template <int DK, int DV, bool ONES>
+void launch_attn(const AttnArgs& a, hipStream_t st) {
+    const AttnSplit sp = attn_split(a, DV);
+    const bool heads = (a.Hq / a.Hkv) % 4 == 0;
+    dim3 grid = sp.keys ? dim3(a.Hq, (a.T + 31) / 32) : heads ? dim3(a.Hq / 4, (a.T + 31) / 32) : dim3(a.Hq, (a.T + 127) / 128);
+    const dim3 block(256);
+    if (sp.runs > 1) {
+        grid.z = sp.runs;
+        if (sp.keys) hipLaunchKernelGGL((attn_keys_kernel<DK, DV, true, ONES>), grid, block, 0, st, a, sp.tps);
+        else if (heads) hipLaunchKernelGGL((attn_kernel<DK, DV, true, true, ONES>), grid, block, 0, st, a, sp.tps);
+        else hipLaunchKernelGGL((attn_kernel<DK, DV, false, true, ONES>), grid, block, 0, st, a, sp.tps);
+        hipLaunchKernelGGL(attn_merge_kernel<DV>, dim3(a.T, a.Hq), dim3(128), 0, st, a, sp.runs);
+        return;
+    }
+    if (sp.keys) hipLaunchKernelGGL((attn_keys_kernel<DK, DV, false, ONES>), grid, block, 0, st, a, 0);
+    else if (heads) hipLaunchKernelGGL((attn_kernel<DK, DV, true, false, ONES>), grid, block, 0, st, a, 0);
+    else hipLaunchKernelGGL((attn_kernel<DK, DV, false, false, ONES>), grid, block, 0, st, a, 0);
 }
 
 }  // namespace
@@ -443,3 +713,19 @@ void attention(const AttnArgs& a, hipStream_t st) {
 }
 
 }  // namespace dlk
+
+// For tests (host only): whether a call goes to attn_keys_kernel, and in how many runs of keys.
+extern "C" __attribute__((visibility("default"))) int32_t dlk_attn_split(int32_t T, int32_t S, int32_t Hq, int32_t Hkv, int32_t dh, uint64_t scratch,
+                                                                         int32_t* runs) {
+    dlk::AttnArgs a{};
+    a.T = T;
+    a.S = S;
+    a.Hq = Hq;
+    a.Hkv = Hkv;
+    float unused;
+    a.split_ws = scratch ? &unused : nullptr;
+    a.split_ws_bytes = scratch;
+    const dlk::AttnSplit s = dlk::attn_split(a, dh <= 64 ? 64 : (dh <= 96 ? 96 : 128));
+    *runs = s.runs;
+    return s.keys ? 1 : 0;
+}

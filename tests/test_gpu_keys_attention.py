@@ -1,0 +1,98 @@
+"""Few queries over many keys: the attention kernel whose four wavefronts take the K/V tiles of one head in turn.  Wavefronts without
+a tile, a ragged last tile, tiles that are masked for a part or all of a query block, one to several runs of keys, every padded
+head dimension (with and without the row of ones), grouped and single KV heads, with a cache and without; one attention block
+against the oracle, the feed-forward zeroed, judged on what it adds to its input (bf16 operands, bound of the other block tests)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from oracle import forward as F
+from paper_2605_11678_amd import binding as B
+from paper_2605_11678_amd import configs as CFG
+from tests.gpu_common import GpuStack
+
+TOL = 2e-2
+
+
+def split_of(T, S, Hq, Hkv, dh, scratch):
+    """(takes the kernel, runs of keys)"""
+    runs = ctypes.c_int32()
+    f = B.lib().dlk_attn_split
+    f.argtypes = [ctypes.c_int32] * 5 + [ctypes.c_uint64, ctypes.POINTER(ctypes.c_int32)]
+    return bool(f(T, S, Hq, Hkv, dh, scratch, ctypes.byref(runs))), runs.value
+
+
+def scratch_of(c, T):
+    """bytes that a call of T tokens may use (a module with a cache)"""
+    mid = 2 * T * c.d_ff // 256 * 256 if T <= 128 and c.d_ff % 128 == 0 else 0
+    return mid + 4 * c.n_q_heads * ((c.max_seq + 63) // 64) * (c.d_head + 2) if T <= 128 else 0
+
+
+# (Hq, Hkv, dh, d_ff, prefix, tokens): decoder chunks.  Runs of keys: 1 but for the two marked
+CHUNKS = [(4, 4, 64, 768, 193, 31), (4, 1, 64, 768, 192, 33), (8, 2, 128, 1024, 260, 64), (8, 2, 128, 1024, 255, 130), (4, 4, 40, 512, 500, 5),
+          (4, 4, 88, 1024, 330, 97), (4, 4, 96, 1024, 321, 32), (8, 1, 120, 1024, 321, 200), (4, 4, 64, 768, 0, 330),
+          (32, 8, 128, 12288, 1500, 19), (16, 4, 64, 4096, 1999, 45)]
+# (Hq, dh, patches): encoder blocks, no cache
+BLOCKS = [(16, 72, 400), (4, 72, 321), (2, 128, 400), (3, 40, 321), (2, 64, 193), (2, 96, 449)]
+
+
+def test_rule():
+    """What takes the kernel, and what does not: one tile, many workgroups, a split that gives the other kernel short runs."""
+    big = 1 << 30
+    assert split_of(128, 3200, 32, 8, 128, 0) == (True, 1) and split_of(800, 3872, 32, 8, 128, 0) == (False, 1)
+    assert split_of(64, 64, 8, 8, 128, big) == (False, 1) and split_of(64, 3072, 8, 8, 128, big) == (False, 16)
+    assert split_of(19, 3091, 32, 8, 128, 4 * 19 * 32 * 132 * 4)[0] and split_of(2, 3074, 32, 8, 128, big)[0] is False
+    assert split_of(731, 731, 16, 16, 72, 0) == (False, 1) and split_of(400, 400, 16, 16, 72, 0) == (True, 1)
+    for T in (1, 2, 31, 32, 33, 128, 129, 500, 4096):
+        for S in (1, 63, 64, 65, 511, 512, 5000):
+            for Hq, Hkv in ((1, 1), (4, 1), (8, 2), (16, 16), (256, 1)):
+                for scratch in (0, 1, 1 << 16, big):
+                    keys, runs = split_of(T, S, Hq, Hkv, 64, scratch)
+                    assert 1 <= runs <= 16 and (runs == 1 or (T <= 128 and S > 448 and runs * Hq * T * 68 * 4 <= scratch)), (T, S, Hq, Hkv, scratch)
+
+
+def attention_only(c):
+    full = CFG.make_layer_weights(c, 0, 1.28)
+    return {k: (np.zeros_like(v) if k in (CFG.T_W_DOWN, CFG.T_B_DOWN) else v) for k, v in full.items()}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,dh,d_ff,prefix,T", CHUNKS)
+def test_chunk(Hq, Hkv, dh, d_ff, prefix, T):
+    c = CFG.ModuleConfig("keys", 1, 256, Hq, Hkv, dh, d_ff, CFG.NORM_RMS, CFG.ACT_SWIGLU, 0, 1, 1e6, max_seq=prefix + T + 3, seed_base=4900)
+    keys, runs = split_of(T, prefix + T, Hq, Hkv, dh, scratch_of(c, T))
+    assert keys and (runs > 1) == (prefix > 1000)
+    gen = lambda l: attention_only(c)
+    x = CFG.make_tokens(prefix + T, c.d_model, seed=37)
+    W = {k: F.widen(v) for k, v in gen(0).items()}
+    kv = {"k": np.zeros((prefix + T, Hkv, dh)), "v": np.zeros((prefix + T, Hkv, dh))}
+    if prefix:
+        kv["k"][:prefix], kv["v"][:prefix] = F.project_kv(c.as_dict(), W, x[:prefix].astype(np.float64))
+    want = F.layer_forward(c.as_dict(), W, x[prefix:].astype(np.float64), prefix, kv)
+    g = GpuStack(c, max_tokens=prefix + T, cap_bytes=512 << 20, weights=gen)
+    try:
+        if prefix:
+            g.forward(x[:prefix])
+        bits = g.forward_bits(x[prefix:], pos0=prefix)
+        assert np.array_equal(bits, g.forward_bits(x[prefix:], pos0=prefix))
+    finally:
+        g.close()
+    got = bits.view(np.float32)
+    assert np.max(np.abs(got - want)) / np.max(np.abs(want - x[prefix:])) <= TOL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,dh,T", BLOCKS)
+def test_block(H, dh, T):
+    c = CFG.ModuleConfig("keys", 1, 256, H, H, dh, 256, CFG.NORM_LN, CFG.ACT_GELU, 1, 0, 0.0, seed_base=4950)
+    assert split_of(T, T, H, H, dh, 0) == (True, 1)
+    w = attention_only(c)
+    x = CFG.make_tokens(T, c.d_model, seed=38)
+    want = F.stack_forward(c.as_dict(), lambda l: w, x)
+    g = GpuStack(c, max_tokens=T, cap_bytes=256 << 20, weights=lambda l: w)
+    try:
+        got = g.forward(x)
+    finally:
+        g.close()
+    assert np.max(np.abs(got - want)) / np.max(np.abs(want - x)) <= TOL
