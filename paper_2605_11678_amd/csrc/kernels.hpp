@@ -123,6 +123,8 @@ void decode_attention(const DecodeAttnArgs& a, hipStream_t st);
 // y[t, :] = mean over j < group of x[t*group + j, :]
 void mean_pool_rows(const float* x, float* y, int T_out, int group, int d, hipStream_t st);
 // y[i] += alpha * x[i]
+// positions [from, to) of `layers` x `rows` V^T rows of ld elements become zero (layers are layer_stride elements apart)
+void zero_positions(bf16_t* vt, uint64_t layer_stride, int layers, int rows, int ld, int from, int to, hipStream_t st);
 void axpy_f32(float* y, float alpha, const float* x, uint64_t n, hipStream_t st);
 // y[t, i] = x[t, i] + (i < d/2 ? sin : cos)(1000 * tval * 10000^(-(i mod d/2) / (d/2)))
 void add_time_embedding(const float* x, float* y, float tval, int T, int d, hipStream_t st);

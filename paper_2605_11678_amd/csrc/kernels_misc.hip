@@ -137,6 +137,12 @@ __global__ __launch_bounds__(256) void mean_pool_kernel(const float* __restrict_
     reinterpret_cast<V*>(y)[i] = o;
 }
 
+__global__ __launch_bounds__(256) void zero_positions_kernel(bf16_t* vt, uint64_t layer_stride, int rows, int ld, int from, int to) {
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int pos = from + (threadIdx.x & 63);             // at most 63 positions
+    if (row < rows && pos < to) vt[uint64_t(blockIdx.y) * layer_stride + uint64_t(row) * uint64_t(ld) + uint64_t(pos)] = 0;
+}
+
 __global__ __launch_bounds__(256) void axpy_kernel(float* __restrict__ y, float alpha, const float* __restrict__ x,
                                                    uint64_t n) {
     for (uint64_t i = uint64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += uint64_t(gridDim.x) * 256)
@@ -401,6 +407,11 @@ __global__ __launch_bounds__(256) void mfma_rate_kernel(float* out, int iters, i
 double mfma_rate_probe(float* out, int blocks, int iters, int pattern, hipStream_t st) {
     hipLaunchKernelGGL(mfma_rate_kernel, dim3(blocks), dim3(256), 0, st, out, iters, pattern);
     return double(blocks) * 4.0 * iters * 16.0 * (2.0 * 32 * 32 * 16);
+}
+
+void zero_positions(bf16_t* vt, uint64_t layer_stride, int layers, int rows, int ld, int from, int to, hipStream_t st) {
+    if (layers <= 0 || rows <= 0 || to <= from) return;
+    hipLaunchKernelGGL(zero_positions_kernel, dim3((rows + 3) / 4, layers), dim3(256), 0, st, vt, layer_stride, rows, ld, from, to);
 }
 
 void axpy_f32(float* y, float alpha, const float* x, uint64_t n, hipStream_t st) {
