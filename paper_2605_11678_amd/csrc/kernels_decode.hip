@@ -38,12 +38,6 @@ __device__ __forceinline__ float dot8(u32x4 w, u32x4 x) {
     return s;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 
 // a "unit" is one output element; for SwiGLU it needs two weight rows (gate and up)
 // ROWS: rows a wavefront streams together (4: two SwiGLU units = 2 gate + 2 up rows, or four plain units; 2 for
@@ -159,7 +153,7 @@ __global__ __launch_bounds__(256) void gemv_kernel(GemvArgs p) {
         }
     }
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) acc[r] = wave_sum(acc[r]);
+    for (int r = 0; r < ROWS; ++r) acc[r] = normdev::wave_sum(acc[r]);
     if (lane != 0) return;
 #pragma unroll
     for (int u = 0; u < UNITS_PER_WAVE; ++u) {
