@@ -467,12 +467,13 @@ void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const floa
 
     // attention sub-block.  A single-token pass has no normalisation launches: the matrix-vector kernels of the
     // QKV projection and of the feed-forward's first map normalise their input row themselves.
+    // Several rows of a narrow model: the products normalise theirs too (dlk::gemm_normed), else `normalise` comes first.
     const bool fused_norm = T == 1;
-    if (!fused_norm) {
+    auto normalise = [&](const float* x, const bf16_t* g, const bf16_t* b) {
         kbegin(DL_K_NORM, 0, Td * dm * 6.0);
-        dlk::norm_rows(d.norm, in, P(L.norm1_g), P(L.norm1_b), nbuf, false, T, dm, d.norm_eps, st);
+        dlk::norm_rows(d.norm, x, g, b, nbuf, false, T, dm, d.norm_eps, st);
         kend();
-    }
+    };
     bf16_t* kc = nullptr;
     bf16_t* vt;
     uint64_t k_hs, v_hs;
@@ -496,9 +497,9 @@ void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const floa
     // token without a cache goes there too: its one key has the weight 1 whatever the score.)
     dlk::QkvPostArgs qp{qkv, L.n_qkv, T, pos0, Hq, Hkv, dh, d.rope_theta, kc, k_hs, vt, v_hs, ldv, 0, dq, dq + dkv};
     lin_work(Td, L.n_qkv, dm, &fl, &by);
-    kbegin(DL_K_GEMM_QKV, fl, by);
     if (T == 1) {
         // single token: rotary embedding and the append to the K / V^T caches happen in the product's epilogue
+        kbegin(DL_K_GEMM_QKV, fl, by);
         dlk::GemvArgs g{nullptr, P(L.w_qkv), dm, P(L.b_qkv), qkv, nullptr, L.n_qkv, dm, dlk::EPI_QKV_POST, qp};
         with_norm(g, NormSrc{in, P(L.norm1_g), P(L.norm1_b), d.norm, d.norm_eps});
         dlk::gemv(g, st);
@@ -506,9 +507,14 @@ void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const floa
     } else {
         const dlk::GemmArgs g{nbuf, dm, P(L.w_qkv), dm, P(L.b_qkv), qkv, L.n_qkv, nullptr, 0, T, L.n_qkv, dm, dlk::EPI_BF16,
                               vt + pos0, dq + dkv, ldv, dlk::attention_q_scale(dh), dq};
-        const bool post = d.rope_theta > 0.0f || kc;
-        const bool fused = d.rope_theta > 0.0f && dlk::gemm_qkv_post(g, qp, st);
-        if (!fused) dlk::gemm(g, st);
+        const bool rope = d.rope_theta > 0.0f, post = rope || kc;
+        const dlk::NormIn n1{in, P(L.norm1_g), P(L.norm1_b), d.norm, d.norm_eps};
+        const bool normed = dlk::gemm_takes_norm(g, n1, rope ? &qp : nullptr);
+        if (!normed) normalise(in, P(L.norm1_g), P(L.norm1_b));
+        kbegin(DL_K_GEMM_QKV, fl, by);
+        if (normed) dlk::gemm_normed(g, n1, rope ? &qp : nullptr, st);
+        const bool fused = rope && (normed || dlk::gemm_qkv_post(g, qp, st));
+        if (!normed && !fused) dlk::gemm(g, st);
         kend();
         if (post && !fused) {
             kbegin(DL_K_QKV_POST, 0, Td * (dq + dkv) * 4.0);
@@ -559,9 +565,16 @@ void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const floa
         const bool make_kv = sc.first || !sc.kv;
         kbegin(DL_K_CROSS, 2.0 * (2.0 * Td * dq * dm + (make_kv ? 2.0 * double(n_ctx) * dkv * d.d_ctx : 0.0)) + 4.0 * dh * Hq * Td * n_ctx,
                2.0 * (2.0 * double(dq) * dm + (make_kv ? 2.0 * double(dkv) * d.d_ctx : 0.0)));
-        dlk::norm_rows(d.norm, out, P(L.normc_g), P(L.normc_b), nbuf, false, T, dm, d.norm_eps, st);
-        linear(st, T, nbuf, dm, P(L.w_qc), dm, dq, P(L.b_qc), dlk::EPI_BF16, qkv, dq, nullptr, 0, NormSrc(), nullptr, 0, 0,
-               dlk::attention_q_scale(dh), dq);
+        const dlk::GemmArgs gq{nbuf, dm, P(L.w_qc), dm, P(L.b_qc), qkv, dq, nullptr, 0, T, dq, dm, dlk::EPI_BF16, nullptr, 0, 0,
+                               dlk::attention_q_scale(dh), dq};
+        const dlk::NormIn nc{out, P(L.normc_g), P(L.normc_b), d.norm, d.norm_eps};
+        if (dlk::gemm_takes_norm(gq, nc, nullptr)) {
+            dlk::gemm_normed(gq, nc, nullptr, st);
+        } else {
+            dlk::norm_rows(d.norm, out, P(L.normc_g), P(L.normc_b), nbuf, false, T, dm, d.norm_eps, st);
+            linear(st, T, nbuf, dm, P(L.w_qc), dm, dq, P(L.b_qc), dlk::EPI_BF16, qkv, dq, nullptr, 0, NormSrc(), nullptr, 0, 0,
+                   dlk::attention_q_scale(dh), dq);
+        }
         // the context is the same for every layer of a pass: layer 0 converts it to bf16 for all of them (a pass
         // always starts at layer 0, and nothing else writes this buffer); later passes of the same call find it converted
         if (layer == 0 && sc.first) dlk::cast_f32_bf16(ctx, ctxn, uint64_t(n_ctx) * d.d_ctx, st);
@@ -581,20 +594,18 @@ void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const floa
     }
 
     // feed-forward sub-block
-    NormSrc n2;
-    if (fused_norm) {
-        n2 = NormSrc{out, P(L.norm2_g), P(L.norm2_b), d.norm, d.norm_eps};
-    } else {
-        kbegin(DL_K_NORM, 0, Td * dm * 6.0);
-        dlk::norm_rows(d.norm, out, P(L.norm2_g), P(L.norm2_b), nbuf, false, T, dm, d.norm_eps, st);
-        kend();
-    }
+    const bool swiglu = d.act == DL_ACT_SWIGLU;
+    const bf16_t* b_up = swiglu ? nullptr : P(L.b_up);
+    const int up_epi = swiglu ? dlk::EPI_SWIGLU_BF16 : dlk::EPI_GELU_BF16;
+    const dlk::GemmArgs gu{nbuf, dm, P(L.w_up), dm, b_up, mid, L.ffp, nullptr, 0, T, L.n_up, dm, up_epi};
+    const dlk::NormIn n2{out, P(L.norm2_g), P(L.norm2_b), d.norm, d.norm_eps};
+    const bool normed2 = dlk::gemm_takes_norm(gu, n2, nullptr);
+    if (!fused_norm && !normed2) normalise(out, P(L.norm2_g), P(L.norm2_b));
     lin_work(Td, L.n_up, dm, &fl, &by);
     kbegin(DL_K_GEMM_UP, fl, 2.0 * (Td * dm + double(L.n_up) * dm + Td * d.d_ff));
-    if (d.act == DL_ACT_SWIGLU)
-        linear(st, T, nbuf, dm, P(L.w_up), dm, L.n_up, nullptr, dlk::EPI_SWIGLU_BF16, mid, L.ffp, nullptr, 0, n2);
-    else
-        linear(st, T, nbuf, dm, P(L.w_up), dm, L.n_up, P(L.b_up), dlk::EPI_GELU_BF16, mid, L.ffp, nullptr, 0, n2);
+    if (normed2) dlk::gemm_normed(gu, n2, nullptr, st);
+    else linear(st, T, nbuf, dm, P(L.w_up), dm, L.n_up, b_up, up_epi, mid, L.ffp, nullptr, 0,
+                fused_norm ? NormSrc{out, P(L.norm2_g), P(L.norm2_b), d.norm, d.norm_eps} : NormSrc());
     kend();
     lin_work(Td, dm, d.d_ff, &fl, &by);
     kbegin(DL_K_GEMM_DOWN, fl, by + 8.0 * Td * dm);

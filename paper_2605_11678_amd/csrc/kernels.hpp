@@ -56,6 +56,18 @@ void qkv_post(const QkvPostArgs& a, hipStream_t st);
 // head dimensions of whole 32-column tiles.  Returns false, with nothing launched, otherwise.
 bool gemm_qkv_post(const GemmArgs& a, const QkvPostArgs& q, hipStream_t st);
 
+// The product of normalised rows (x[M,K] fp32, kind, gains and biases as in norm_rows, rounded to bf16) in one launch, with q != nullptr
+// what gemm_qkv_post does besides; a.A is not read.  Only for what gemm_takes_norm accepts: 2 .. 64 rows, 64 KB of them at most.
+struct NormIn {
+    const float* x;
+    const bf16_t* g;
+    const bf16_t* b;
+    int kind;
+    float eps;
+};
+bool gemm_takes_norm(const GemmArgs& a, const NormIn& n, const QkvPostArgs* q);
+void gemm_normed(const GemmArgs& a, const NormIn& n, const QkvPostArgs* q, hipStream_t st);
+
 // ---- matrix-vector for single-token passes: out[N] = B[N,K] * x[K], same epilogues ----------
 struct GemvArgs {
     const bf16_t* x;              // [K] bf16

@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "norm_device.hpp"
 
 namespace dlk {
 
@@ -114,16 +115,26 @@ struct Stages {
 // 76 us (128x128 register-staged kernel) -> 39, against 32 for its weights at the rate of a streaming read.
 // EPI_QKV_POST: a tile of q or k columns takes BN / 2 columns and their rotary partners dh / 2 further on, scales and rounds them like a
 // plain product's, rotates and scatters them (a layer over 19 rows and 3072 cached: 122.2 us with the separate launch, now 119.8).
+// NORM >= 0: A is the normalisation (KIND as in norm_rows) of fp32 rows, which every workgroup makes for itself and keeps in LDS, all
+// k-tiles of it; only weights are staged.  The rows are requested in front of the first weights, and at most 64 KB of them: a
+// workgroup takes them in at ~60 bytes per ns, in about a microsecond, where a launch of its own takes 3.3 and the gap in front of it.
 // Rows past M repeat row M - 1 and are not stored.  Needs K % 64 == 0, N % 16 == 0, 16-byte aligned rows.
 struct NoPost {};
 template <int EPI>
 using PostArgs = std::conditional_t<EPI == EPI_QKV_POST, QkvPostArgs, NoPost>;
-template <int BM, int BN, int NS, int EPI>
-__global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> post) {
-    constexpr int W = 4, STG = (BM + BN) * 64;           // wavefronts; elements of one wavefront's stage
-    constexpr int JA = BM / 8, JB = BN / 8, TM = BM / 16, TN = BN / 16;
+struct NoNorm {};
+template <int NORM>
+using NormArgs = std::conditional_t<(NORM >= 0), NormIn, NoNorm>;
+// longest reduction of the kernel with NORM
+constexpr int max_norm_k(int bm) { return 256 * (64 / bm); }
+template <int BM, int BN, int NS, int EPI, int NORM>
+__global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> post, NormArgs<NORM> nrm) {
+    constexpr bool NA = NORM >= 0;
+    constexpr int W = 4, STG = (NA ? BN : BM + BN) * 64;  // wavefronts; elements of one wavefront's stage
+    constexpr int JA = NA ? 0 : BM / 8, JB = BN / 8, TM = BM / 16, TN = BN / 16;
     typedef __attribute__((ext_vector_type(4))) float f32x4;
     DL_STAGES(st, NS, W * STG)
+    extern __shared__ __attribute__((aligned(1024))) bf16_t normed[];    // NORM: [k-tile][row][64], chunks swizzled as in the stages
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nk = p.K >> 6;
     const int n_my = (nk - wave + W - 1) / W;            // k-tiles wave, wave + W, ... (0 when there are fewer than wavefronts)
@@ -142,7 +153,7 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
     };
     // the host takes this kernel only for operands below 4 GB
     const int sizeA = int(uint32_t(size_t(p.M) * p.lda * 2)), sizeB = int(uint32_t(size_t(p.N) * p.ldb * 2));
-    uint32_t offA[JA], offB[JB];
+    uint32_t offA[JA + 1], offB[JB];
 #pragma unroll
     for (int j = 0; j < JA; ++j) {
         const int row = 8 * j + (lane >> 3), lc = (lane & 7) ^ ((row >> 1) & 7);
@@ -177,14 +188,15 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
         DL_WAIT_VM((REM < NS - 1 ? REM : NS - 1) * (JA + JB));
         __builtin_amdgcn_sched_barrier(0);
         const bf16_t* d = S + wave * STG;
+        const bf16_t* da = NA ? normed + (wave + W * i < nk ? wave + W * i : 0) * (BM * 64) : d;   // (what is not there meets zeros)
         bf16x8 a[2][TM], b[2][TN];
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
             const int pc = ((4 * kk + lg) ^ ((lr >> 1) & 7)) * 8;
 #pragma unroll
-            for (int t = 0; t < TM; ++t) a[kk][t] = *reinterpret_cast<const bf16x8*>(d + (16 * t + lr) * 64 + pc);
+            for (int t = 0; t < TM; ++t) a[kk][t] = *reinterpret_cast<const bf16x8*>(da + (16 * t + lr) * 64 + pc);
 #pragma unroll
-            for (int t = 0; t < TN; ++t) b[kk][t] = *reinterpret_cast<const bf16x8*>(d + (BM + 16 * t + lr) * 64 + pc);
+            for (int t = 0; t < TN; ++t) b[kk][t] = *reinterpret_cast<const bf16x8*>(d + (8 * JA + 16 * t + lr) * 64 + pc);
         }
         if constexpr (REM >= NS) {
             __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): the fragments are in registers, the stage is free
@@ -204,8 +216,63 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
         ktile(st.s[I % NS], i0 + I, integral_constant<int, (N - 1 - I + AFTER < NS ? N - 1 - I + AFTER : NS)>{});
         if constexpr (I + 1 < N) self(self, i0, integral_constant<int, I + 1>{}, n_c, after_c);
     };
+    if constexpr (NA) {
+        // a wavefront takes BM / 4 rows, four at a time: 16 lanes to a row, P 16-byte pieces a lane
+        constexpr int P = max_norm_k(BM) / 64, G = BM / W / 4;
+        const int nv = p.K >> 2, l16 = lane & 15;
+        float4 v[G][P];
+        uint2 gk[P], bk[P];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) copy(st.s[s], s, s < n_my);
+        for (int j = 0; j < P; ++j) {
+            const int i = l16 + 16 * j, ic = i < nv ? i : 0;
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+                v[g][j] = reinterpret_cast<const float4*>(nrm.x + size_t(min((wave * G + g) * 4 + (lane >> 4), p.M - 1)) * p.K)[ic];
+            gk[j] = reinterpret_cast<const uint2*>(nrm.g)[ic];
+            if (NORM == 1) bk[j] = reinterpret_cast<const uint2*>(nrm.b)[ic];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) copy(st.s[s], s, s < n_my);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int row = (wave * G + g) * 4 + (lane >> 4);
+            float mean = 0.0f, ss = 0.0f;
+            if (NORM == 1) {
+                float sum = 0.0f;
+#pragma unroll
+                for (int j = 0; j < P; ++j)
+                    if (l16 + 16 * j < nv) sum += (v[g][j].x + v[g][j].y) + (v[g][j].z + v[g][j].w);
+                mean = normdev::row16_sum(sum) / float(p.K);
+            }
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const float a0 = v[g][j].x - mean, a1 = v[g][j].y - mean, a2 = v[g][j].z - mean, a3 = v[g][j].w - mean;
+                if (l16 + 16 * j < nv) ss += (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
+            }
+            const float inv = rsqrtf(normdev::row16_sum(ss) / float(p.K) + nrm.eps);
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const int i = l16 + 16 * j;
+                float o[4] = {(v[g][j].x - mean) * inv * __uint_as_float(gk[j].x << 16), (v[g][j].y - mean) * inv * __uint_as_float(gk[j].x & 0xFFFF0000u),
+                              (v[g][j].z - mean) * inv * __uint_as_float(gk[j].y << 16), (v[g][j].w - mean) * inv * __uint_as_float(gk[j].y & 0xFFFF0000u)};
+                if (NORM == 1) {
+                    o[0] += __uint_as_float(bk[j].x << 16);
+                    o[1] += __uint_as_float(bk[j].x & 0xFFFF0000u);
+                    o[2] += __uint_as_float(bk[j].y << 16);
+                    o[3] += __uint_as_float(bk[j].y & 0xFFFF0000u);
+                }
+                if (i < nv)
+                    *reinterpret_cast<uint2*>(normed + ((i >> 4) * BM + row) * 64 + ((((i >> 1) & 7) ^ ((row >> 1) & 7)) * 8 + (i & 1) * 4)) =
+                        make_uint2(uint32_t(f_to_bf16(o[0])) | (uint32_t(f_to_bf16(o[1])) << 16), uint32_t(f_to_bf16(o[2])) | (uint32_t(f_to_bf16(o[3])) << 16));
+            }
+        }
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) copy(st.s[s], s, s < n_my);
+    }
     const int n_run = n_my < NS ? NS : n_my;             // stages of zeros are multiplied as well: no path for fewer than NS
     int i0 = 0;
     for (; i0 + 2 * NS <= n_run; i0 += NS)
@@ -224,8 +291,8 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
     rest(rest, integral_constant<int, NS>{});
 
     __syncthreads();                                     // everybody is done with the stages
-    float* part = reinterpret_cast<float*>(st.s[0]);
-    static_assert(W * BM * BN * 4 <= W * STG * 2, "the partial tiles fit one stage array");
+    float* part = reinterpret_cast<float*>(NA ? normed : st.s[0]);
+    static_assert(NA || W * BM * BN * 4 <= W * STG * 2, "the partial tiles fit one stage array (or the rows: K >= 128, 16 columns)");
     // accumulator of a 16x16 tile: lane l, register r -> column l % 16, row 4 (l / 16) + r
 #pragma unroll
     for (int t = 0; t < TM; ++t)
@@ -335,7 +402,8 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
 template <int EPI>
 void launch_few_rows(const GemmArgs& a, hipStream_t st, const PostArgs<EPI>& post = {}) {
     auto go = [&](auto bm, auto bn, auto ns) {
-        hipLaunchKernelGGL((gemm_few_rows<decltype(bm)::value, decltype(bn)::value, decltype(ns)::value, EPI>), dim3(a.N / bn), dim3(256), 0, st, a, post);
+        hipLaunchKernelGGL((gemm_few_rows<decltype(bm)::value, decltype(bn)::value, decltype(ns)::value, EPI, -1>), dim3(a.N / bn), dim3(256), 0, st, a,
+                           post, NoNorm{});
     };
     using std::integral_constant;
     const integral_constant<int, 16> c16{};
@@ -345,6 +413,22 @@ void launch_few_rows(const GemmArgs& a, hipStream_t st, const PostArgs<EPI>& pos
     else if (a.M <= 32) go(c32, c16, integral_constant<int, 3>{});
     else if (a.N % 32 == 0 && a.N > 256 * 16) go(c64, c32, integral_constant<int, 3>{});
     else go(c64, c16, integral_constant<int, 2>{});
+}
+
+// With the normalisation: all k-tiles of a wavefront staged at once (K at most 256, 512 and 1024 for 64, 32 and 16 rows).
+template <int EPI, int NORM>
+void launch_few_rows_norm(const GemmArgs& a, const NormIn& n, hipStream_t st, const PostArgs<EPI>& post) {
+    const int bm = a.M <= 16 ? 16 : (a.M <= 32 ? 32 : 64);
+    const dim3 grid(a.N / 16), block(256);
+    const size_t lds = size_t(a.K) * bm * 2;
+    if (bm == 16) hipLaunchKernelGGL((gemm_few_rows<16, 16, 4, EPI, NORM>), grid, block, lds, st, a, post, n);
+    else if (bm == 32) hipLaunchKernelGGL((gemm_few_rows<32, 16, 2, EPI, NORM>), grid, block, lds, st, a, post, n);
+    else hipLaunchKernelGGL((gemm_few_rows<64, 16, 2, EPI, NORM>), grid, block, lds, st, a, post, n);
+}
+template <int EPI>
+void launch_few_rows_norm(const GemmArgs& a, const NormIn& n, hipStream_t st, const PostArgs<EPI>& post = {}) {
+    if (n.kind == 0) launch_few_rows_norm<EPI, 0>(a, n, st, post);
+    else launch_few_rows_norm<EPI, 1>(a, n, st, post);
 }
 
 // Column tiles whose residual values are requested together: what fits next to the accumulators without spilling (TM = 3: all of
@@ -1072,12 +1156,32 @@ bool takes_few_rows(const GemmArgs& a) {
 
 }  // namespace
 
+namespace {
+// (the product is one of gemm_few_rows' with the rotary epilogue)
+bool takes_qkv_post(const GemmArgs& a, const QkvPostArgs& q) {
+    return a.M >= 1 && a.N >= 1 && a.vt && !takes_tiles(a) && takes_few_rows(a) && q.dh % 32 == 0 && q.q_off == 0 && q.k_off % q.dh == 0 &&
+           a.vt_col % q.dh == 0 && a.out == q.qkv && a.ldo == q.n_qkv;
+}
+}  // namespace
+
 bool gemm_qkv_post(const GemmArgs& a, const QkvPostArgs& q, hipStream_t st) {
-    if (a.M < 1 || a.N < 1 || !a.vt || takes_tiles(a) || !takes_few_rows(a) || q.dh % 32 != 0 || q.q_off != 0 || q.k_off % q.dh != 0 ||
-        a.vt_col % q.dh != 0 || a.out != q.qkv || a.ldo != q.n_qkv)
-        return false;
+    if (!takes_qkv_post(a, q)) return false;
     launch_few_rows<EPI_QKV_POST>(a, st, q);
     return true;
+}
+
+bool gemm_takes_norm(const GemmArgs& a, const NormIn& n, const QkvPostArgs* q) {
+    const int bm = a.M <= 16 ? 16 : (a.M <= 32 ? 32 : 64);
+    return a.M > 1 && a.N >= 1 && !takes_tiles(a) && takes_few_rows(a) && a.K >= 128 && a.K <= max_norm_k(bm) && a.lda == a.K &&
+           (reinterpret_cast<uintptr_t>(n.x) | reinterpret_cast<uintptr_t>(n.g) | reinterpret_cast<uintptr_t>(n.b)) % 16 == 0 &&
+           (q ? takes_qkv_post(a, *q) : a.epi == EPI_BF16 || a.epi == EPI_SWIGLU_BF16 || a.epi == EPI_GELU_BF16);
+}
+
+void gemm_normed(const GemmArgs& a, const NormIn& n, const QkvPostArgs* q, hipStream_t st) {
+    if (q) launch_few_rows_norm<EPI_QKV_POST>(a, n, st, *q);
+    else if (a.epi == EPI_BF16) launch_few_rows_norm<EPI_BF16>(a, n, st);
+    else if (a.epi == EPI_SWIGLU_BF16) launch_few_rows_norm<EPI_SWIGLU_BF16>(a, n, st);
+    else launch_few_rows_norm<EPI_GELU_BF16>(a, n, st);
 }
 
 void gemm(const GemmArgs& a, hipStream_t st) {

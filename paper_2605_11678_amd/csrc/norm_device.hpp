@@ -16,15 +16,19 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_add(float v) {
     return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
+// over each 16 lanes
+__device__ __forceinline__ float row16_sum(float v) {
+    v = dpp_add<0x128>(v);         // row_ror 8
+    v = dpp_add<0x124>(v);         // row_ror 4: lanes 8 apart are equal by now
+    v = dpp_add<0x4E>(v);          // quad_perm [2, 3, 0, 1]
+    return dpp_add<0xB1>(v);       // quad_perm [1, 0, 3, 2]
+}
 __device__ __forceinline__ float wave_sum(float v) {
     const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
     const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
-    v = dpp_add<0x128>(v);         // row_ror 8
-    v = dpp_add<0x124>(v);         // row_ror 4: lanes 8 apart are equal by now
-    v = dpp_add<0x4E>(v);          // quad_perm [2, 3, 0, 1]
-    return dpp_add<0xB1>(v);       // quad_perm [1, 0, 3, 2]
+    return row16_sum(v);
 }
 
 // sum over a 256-thread block; every thread gets the result
