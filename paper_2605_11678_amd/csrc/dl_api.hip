@@ -44,13 +44,21 @@ hipError_t static_scratch_ptr(int32_t device, void** out) {
     return hipSuccess;
 }
 
+// Logits up to here (64 KB) come to the host by the kernel that looks for the largest, into pinned memory, and the host copies them on:
+// head, choice and logits of 1024 / 4096 / 16384 take 21.9 / 23.2 / 28.6 us that way, 32.6 / 33.6 / 39.9 with a copy into the caller's
+// pageable memory behind the launch.  More of them keep that copy (32768: 45.7 us): a module does not pin more than this for it.
+constexpr int32_t kPinnedLogits = 16384;
+uint64_t head_host_bytes(const dl_module_desc& d) {
+    return d.vocab <= 0 ? 0 : 256 + (d.vocab <= kPinnedLogits ? 4 * uint64_t(d.vocab) : 0);
+}
+
 struct Module {
     dl_module_desc d{};
     PackLayout L;
     dl::WorkspaceLayout W;
     dl::KvLayout KV;
     // n_layers blobs, pinned (or plain malloc in a host-only context); with a head, 256 bytes behind them for the token that
-    // dl_logits_argmax's kernel chooses, so that only the logits are copied
+    // dl_logits_argmax's kernel chooses, and with a small one (kPinnedLogits) its logits, which the kernel leaves there too
     uint8_t* store = nullptr;
     std::vector<uint32_t> set_mask;      // per layer: which tensors have been provided
     bool finalized = false;
@@ -844,7 +852,7 @@ int32_t dl_module_create(dl_ctx* c, const dl_module_desc* desc, int32_t* module_
     M.L = dl::make_layout(*desc);
     M.W = dl::make_workspace(*desc);
     M.KV = dl::make_kv(*desc);
-    const uint64_t total = uint64_t(desc->n_layers) * M.L.bytes + (desc->vocab > 0 ? 256 : 0);   // (see Module::store)
+    const uint64_t total = uint64_t(desc->n_layers) * M.L.bytes + head_host_bytes(*desc);   // (see Module::store)
     if (on_gpu(c)) {
         void* p = nullptr;
         if (hipHostMalloc(&p, total, hipHostMallocDefault) != hipSuccess || !p) {
@@ -1036,7 +1044,8 @@ int32_t dl_final_norm(dl_ctx* c, int32_t module, const void* h, void* out, int32
 
 // final norm + head + greedy choice; with x_next != nullptr the chosen token's embedding row is written there (and the
 // token to token_copy, if given) by the same launch that picks it
-static int32_t head_common(dl_ctx* c, Module* M, const void* h, int32_t* token_copy = nullptr, float* x_next = nullptr) {
+static int32_t head_common(dl_ctx* c, Module* M, const void* h, int32_t* token_copy = nullptr, float* x_next = nullptr,
+                           float* logits_copy = nullptr) {
     if (!M || !M->finalized) return fail(c, DL_ERR_BAD_STATE, "module missing or not finalized");
     if (M->d.vocab <= 0 || !M->rt_set[DL_R_HEAD] || !M->rt_set[DL_R_FINAL_NORM_G] ||
         (M->d.norm == DL_NORM_LN && !M->rt_set[DL_R_FINAL_NORM_B]))
@@ -1060,7 +1069,7 @@ static int32_t head_common(dl_ctx* c, Module* M, const void* h, int32_t* token_c
     dlk::gemv(g, st);
     dlk::argmax_f32(logits, M->d.vocab, tok, token_copy,
                     x_next ? reinterpret_cast<const bf16_t*>(c->base + M->rt_off[DL_R_EMBED]) : nullptr, M->d.d_model, x_next,
-                    st);
+                    st, logits_copy);
     DL_HIP(c, hipGetLastError());
     return DL_OK;
 }
@@ -1071,14 +1080,16 @@ int32_t dl_logits_argmax(dl_ctx* c, int32_t module, const void* h, int32_t* toke
     Module* M = get_module(c, module);
     if (!token_out) return fail(c, DL_ERR_INVALID_ARG, "null token_out");
     int32_t* const token_host = M && M->d.vocab > 0 ? reinterpret_cast<int32_t*>(M->store + size_t(M->d.n_layers) * M->L.bytes) : nullptr;
-    rc = head_common(c, M, h, token_host);
+    float* const logits_host = logits_out && token_host && M->d.vocab <= kPinnedLogits ? reinterpret_cast<float*>(token_host) + 64 : nullptr;
+    rc = head_common(c, M, h, token_host, nullptr, logits_host);
     if (rc) return rc;
     if (!on_gpu(c)) { *token_out = 0; return DL_OK; }
     uint8_t* ws = c->base + M->ws_off;
-    if (logits_out)
+    if (logits_out && !logits_host)
         DL_HIP(c, hipMemcpyAsync(logits_out, ws + M->W.logits, 4 * size_t(M->d.vocab), hipMemcpyDeviceToHost, c->s_compute));
     DL_HIP(c, hipStreamSynchronize(c->s_compute));
     *token_out = *static_cast<volatile int32_t*>(token_host);
+    if (logits_host) memcpy(logits_out, logits_host, 4 * size_t(M->d.vocab));
     return DL_OK;
 }
 

@@ -152,6 +152,6 @@ void embed_row(const bf16_t* table, int d, const int32_t* token_dev, int token_h
 // token_dev (and token_copy, if not null) = index of the largest logit, lowest index on ties; if table != nullptr also
 // x_out[0..d) = row `token` of the bf16 table [*, d] as fp32 (the next step's input), in the same launch
 void argmax_f32(const float* logits, int n, int32_t* token_dev, int32_t* token_copy, const bf16_t* table, int d,
-                float* x_out, hipStream_t st);
+                float* x_out, hipStream_t st, float* logits_copy = nullptr);
 
 }  // namespace dlk

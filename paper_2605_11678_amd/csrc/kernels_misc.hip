@@ -268,13 +268,13 @@ __global__ __launch_bounds__(256) void embed_kernel(const bf16_t* __restrict__ t
 // Greedy choice and the next input in one launch: index of the largest of v[0..n) (lowest index on ties) written to
 // out0 and, if given, out1; then, if a table is given, row `index` of the bf16 table [*, d] widened to fp32 into
 // x_out.  One 1024-thread workgroup; a thread's values are requested eight at a time with clamped indices before
-// any is compared.
+// any is compared.  v_copy: the values also go there (host memory the caller reads behind the launch).
 __device__ __forceinline__ void take_better(float& best, int& bi, float x, int i) {
     if (x > best || (x == best && i < bi)) { best = x; bi = i; }
 }
 __global__ __launch_bounds__(1024) void argmax_embed_kernel(const float* __restrict__ v, int n, int32_t* __restrict__ out0,
                                                             int32_t* __restrict__ out1, const bf16_t* __restrict__ table,
-                                                            int d, float* __restrict__ x_out) {
+                                                            int d, float* __restrict__ x_out, float* __restrict__ v_copy) {
     __shared__ float sv[16];
     __shared__ int si[16];
     __shared__ int s_tok;
@@ -291,7 +291,10 @@ __global__ __launch_bounds__(1024) void argmax_embed_kernel(const float* __restr
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int i = base + tid + 1024 * j;
-            if (i < n) take_better(best, bi, x[j], i);
+            if (i < n) {
+                take_better(best, bi, x[j], i);
+                if (v_copy) v_copy[i] = x[j];
+            }
         }
     }
 #pragma unroll
@@ -446,9 +449,9 @@ void embed_row(const bf16_t* table, int d, const int32_t* token_dev, int token_h
 }
 
 void argmax_f32(const float* logits, int n, int32_t* token_dev, int32_t* token_copy, const bf16_t* table, int d,
-                float* x_out, hipStream_t st) {
+                float* x_out, hipStream_t st, float* logits_copy) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(argmax_embed_kernel, dim3(1), dim3(1024), 0, st, logits, n, token_dev, token_copy, table, d, x_out);
+    hipLaunchKernelGGL(argmax_embed_kernel, dim3(1), dim3(1024), 0, st, logits, n, token_dev, token_copy, table, d, x_out, logits_copy);
 }
 
 }  // namespace dlk
