@@ -801,7 +801,9 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     // showed every second LDS cycle of the kernel as a bank conflict).  Rows past the matrix edge are clamped: they produce values that the epilogue never stores.
     // Tiles in one row of tiles start at different blocks of their rows of A, tiles in one column at different blocks of B:
     // those that run on an XCD at the same time then ask its L2 for a line one after the other, and all but the first find it there.
-    const int rotA = n0 / BN * ((JA + 3) / 4) % JA, rotB = m0 / BM * ((JB + 3) / 4) % JB;
+    // (not on 256x256: there the MFMAs hide them, and 4096^3 with an fp32 output took 1.5 us more.)
+    constexpr bool ROT = BM * BN < 256 * 256;
+    const int rotA = ROT ? n0 / BN * ((JA + 3) / 4) % JA : 0, rotB = ROT ? m0 / BM * ((JB + 3) / 4) % JB : 0;
     uint32_t offA[JA], offB[JB];
     int blkA[JA], blkB[JB];
 #pragma unroll
@@ -874,13 +876,14 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     // first of the next k-tile, A of kt+SA in the two that follow.  Four phases with a quarter of the copies each: a wavefront
     // that issues more at a time waits in front of the copy path, and its MFMAs with it (256 x 128 wavefront pairs, 128x256 on three:
     // 4096^3 116.5 -> 111.6 us, 4096 x 1152, K = 4352: 48.0 -> 44.8).  On two stages there is no time for that, a copy has to land
-    // within a k-tile: B goes with the last phase, A with the first.
+    // within a k-tile: A goes with the last phase, B with the first (the other way round, 256x256 with 4096^3 and an fp32 output took
+    // 2 us more).
     // 192x256 and 256x192 have two stages of the operand with more to copy and four or three of the other: half of the copies get a
     // k-tile or two more to land (192x256: 3072 x 4096, K = 12288, 238 -> 220 us; 3072 x 6144, K = 4096, 156 -> 137).
     // REM = k-tiles after this one, capped at SA (the steady state): with too few left a copy has nothing to fetch; the wait
     // leaves the copies younger than k-tile kt+1 in flight.
     constexpr bool SPREAD = SA > 2;
-    constexpr int B0 = SPREAD ? JB / 2 : JB, A0 = SPREAD ? 0 : JA, A1 = SPREAD ? JA / 2 : JA;
+    constexpr int B0 = SPREAD ? JB / 2 : 0, A1 = SPREAD ? JA / 2 : JA;
     constexpr int U = SA % SB == 0 ? SA : SA * SB;       // k-tiles until the stages come round
     auto ktile = [&](auto i_c, int kt, auto rem_c) {
         constexpr int I = decltype(i_c)::value, REM = decltype(rem_c)::value;
@@ -888,13 +891,12 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
         bf16_t *ca = sa.s[I % SA], *cb = sb.s[I % SB], *pa = sa.s[(I + SA - 1) % SA], *pb = sb.s[(I + SB - 1) % SB];
         ldfrag(a1, b1, ca, cb, 1);
         if (kB1) copyB(pb, kt + SB - 1, B0, JB);
-        if (kA) copyA(pa, kt + SA - 1, 0, A0);
         mma(a0, b0);
-        interleave(std::integral_constant<int, (kB1 ? JB - B0 : 0) + (kA ? A0 : 0)>{});
+        interleave(std::integral_constant<int, (kB1 ? JB - B0 : 0)>{});
         ldfrag(a0, b0, ca, cb, 2);
-        if (kA) copyA(pa, kt + SA - 1, A0, A1);
+        if (SPREAD && kA) copyA(pa, kt + SA - 1, 0, A1);
         mma(a1, b1);
-        interleave(std::integral_constant<int, (kA ? A1 - A0 : 0)>{});
+        interleave(std::integral_constant<int, (SPREAD && kA ? A1 : 0)>{});
         ldfrag(a1, b1, ca, cb, 3);
         if (kA) copyA(pa, kt + SA - 1, A1, JA);
         mma(a0, b0);
@@ -908,8 +910,9 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
             __builtin_amdgcn_sched_barrier(0);
             ldfrag(a0, b0, sa.s[(I + 1) % SA], sb.s[(I + 1) % SB], 0);
             if (kB) copyB(cb, kt + SB, 0, B0);
+            if (!SPREAD && kB) copyA(ca, kt + SA, 0, JA);
             mma(a1, b1);
-            interleave(std::integral_constant<int, (kB ? B0 : 0)>{});
+            interleave(std::integral_constant<int, (kB ? (SPREAD ? B0 : JA) : 0)>{});
         } else {
             mma(a1, b1);
             __builtin_amdgcn_sched_barrier(0);
@@ -921,10 +924,11 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     for (int s = 0; s < SA; ++s) {
         const int kb = s - (SA - SB);
         if (kb >= 0) copyB(sb.s[kb], kb, 0, s + 1 < SA ? JB : B0);
-        if (s + 1 < SA) copyA(sa.s[s], s, 0, JA);
+        if (s + 1 < SA || !SPREAD) copyA(sa.s[s], s, 0, JA);
     }
-    // k-tile 0 has landed (this wavefront's share): behind B of k-tile 0 come A of SA - SB (SA == SB: 1) .. SA - 2 and B of 1 .. SB - 1
-    DL_WAIT_VM((SA == SB ? SB - 2 : SB - 1) * JA + (SB - 2) * JB + B0);
+    // k-tile 0 has landed (this wavefront's share): behind B of k-tile 0 come A of SA - SB (SA == SB: 1) .. SA - 2 and B of 1 .. SB - 1,
+    // on two stages A of 1
+    DL_WAIT_VM(SPREAD ? (SA == SB ? SB - 2 : SB - 1) * JA + (SB - 2) * JB + B0 : JA);
     __builtin_amdgcn_s_barrier();
     ldfrag(a0, b0, sa.s[0], sb.s[0], 0);
     __builtin_amdgcn_sched_barrier(0);
