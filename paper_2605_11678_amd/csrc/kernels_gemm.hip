@@ -188,7 +188,9 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
         DL_WAIT_VM((REM < NS - 1 ? REM : NS - 1) * (JA + JB));
         __builtin_amdgcn_sched_barrier(0);
         const bf16_t* d = S + wave * STG;
-        const bf16_t* da = NA ? normed + (wave + W * i < nk ? wave + W * i : 0) * (BM * 64) : d;   // (what is not there meets zeros)
+        // a k-tile that is not there has zeros for B; NORM has none for A: an infinity of another k-tile must not meet them
+        const bool there = !NA || wave + W * i < nk;
+        const bf16_t* da = NA ? normed + (there ? wave + W * i : 0) * (BM * 64) : d;
         bf16x8 a[2][TM], b[2][TN];
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
@@ -203,12 +205,14 @@ __global__ __launch_bounds__(256) void gemm_few_rows(GemmArgs p, PostArgs<EPI> p
             __builtin_amdgcn_sched_barrier(0);
             copy(S, i + NS, true);
         }
+        if (there) {
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
+            for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-            for (int t = 0; t < TM; ++t)
+                for (int t = 0; t < TM; ++t)
 #pragma unroll
-                for (int u = 0; u < TN; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk][t], b[kk][u], acc[t][u], 0, 0, 0);
+                    for (int u = 0; u < TN; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk][t], b[kk][u], acc[t][u], 0, 0, 0);
+        }
     };
     using std::integral_constant;
     auto run = [&](auto self, int i0, auto i_c, auto n_c, auto after_c) {
