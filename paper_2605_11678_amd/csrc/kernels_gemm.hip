@@ -116,8 +116,8 @@ struct Stages {
 // EPI_QKV_POST: a tile of q or k columns takes BN / 2 columns and their rotary partners dh / 2 further on, scales and rounds them like a
 // plain product's, rotates and scatters them (a layer over 19 rows and 3072 cached: 122.2 us with the separate launch, now 119.8).
 // NORM >= 0: A is the normalisation (KIND as in norm_rows) of fp32 rows, which every workgroup makes for itself and keeps in LDS, all
-// k-tiles of it; only weights are staged.  The rows are requested in front of the first weights, and at most 64 KB of them: a
-// workgroup takes them in at ~60 bytes per ns, in about a microsecond, where a launch of its own takes 3.3 and the gap in front of it.
+// k-tiles of it; only weights are staged.  The rows are requested in front of the first weights, and at most 64 KB of them (see
+// norm_pays; more were not measured).
 // Rows past M repeat row M - 1 and are not stored.  Needs K % 64 == 0, N % 16 == 0, 16-byte aligned rows.
 struct NoPost {};
 template <int EPI>
@@ -1178,9 +1178,19 @@ bool gemm_qkv_post(const GemmArgs& a, const QkvPostArgs& q, hipStream_t st) {
     return true;
 }
 
+// Every workgroup makes all rows for itself, which pays for the launch it saves while there is one workgroup to a compute unit and the
+// rows are short.  A product that writes the rows, then normalisation and product in two launches / in one, us: 16 rows, K = 256,
+// RMSNorm 4096 columns 8.2 / 6.9, 8192 8.0 / 8.0, 24576 11.0 / 12.9; LayerNorm 512 columns 7.9 / 7.4, 4096 7.6 / 7.7, 8192 8.2 / 9.1, 24576
+// 11.2 / 15.7; 32 rows 12288 columns 10.0 / 10.2, 16384 10.8 / 11.5; 64 rows 8192 10.6 / 10.5.  16 rows, K = 1024: RMSNorm 2048 columns 7.8 / 7.9,
+// 8192 8.6 / 8.8; LayerNorm 512 columns 8.0 / 8.3, 4096 8.0 / 8.7.
+bool norm_pays(const GemmArgs& a, int kind) {
+    if (a.M > 16 && a.K <= 256) return a.N <= 12288;
+    return a.N <= 4096 && long(a.N) * a.K <= (kind == 1 && a.K > 512 ? 1L << 19 : 1L << 21);
+}
+
 bool gemm_takes_norm(const GemmArgs& a, const NormIn& n, const QkvPostArgs* q) {
     const int bm = a.M <= 16 ? 16 : (a.M <= 32 ? 32 : 64);
-    return a.M > 1 && a.N >= 1 && !takes_tiles(a) && takes_few_rows(a) && a.K >= 128 && a.K <= max_norm_k(bm) && a.lda == a.K &&
+    return a.M > 1 && norm_pays(a, n.kind) && a.N >= 1 && !takes_tiles(a) && takes_few_rows(a) && a.K >= 128 && a.K <= max_norm_k(bm) && a.lda == a.K &&
            (reinterpret_cast<uintptr_t>(n.x) | reinterpret_cast<uintptr_t>(n.g) | reinterpret_cast<uintptr_t>(n.b)) % 16 == 0 &&
            (q ? takes_qkv_post(a, *q) : a.epi == EPI_BF16 || a.epi == EPI_SWIGLU_BF16 || a.epi == EPI_GELU_BF16);
 }
