@@ -650,6 +650,16 @@ struct AttnSplit {
     bool keys;                                             // attn_keys_kernel
     int runs, tps;                                         // runs of tps tiles (1: no second launch)
 };
+// Where attn_kernel is split too the difference is small and goes with the padded head dimension (64, 96, 128; us; share: of a launch of
+// 256 workgroups of attn_keys_kernel).  Fitted to 22548 times of 3680 calls: 2 .. 128 tokens over 140 .. 8100 keys, 4 to 32 heads of 40 ..
+// 128.  With the constants above alone 191 of them were slower than on attn_kernel, by up to 13 % (8 heads of 128, 2 tokens over 700
+// keys: 13.2 us for 11.7; 16 heads, 4000 keys: 16.5 for 15.2); now 21 are by more than 2 %, three by more than 5 % (the worst, 32 KV heads of 128, 19 tokens over 8100
+// keys, where their bytes bound both: 33.0 for 30.1).
+struct AttnTimes {
+    float tile, keys_tile, keys_edge, keys_share;
+};
+constexpr AttnTimes kAttnTimes[] = {{0.6f, 1.0f, 0.2f, 0.2f}, {0.7f, 1.3f, 0.7f, 0.9f}, {0.9f, 1.5f, 1.0f, 2.0f}};
+
 AttnSplit attn_split(const AttnArgs& a, int dv) {
     const int nt = (a.S + BKV - 1) / BKV, qb = (a.T + 31) / 32;
     const bool heads = (a.Hq / a.Hkv) % 4 == 0;
@@ -665,7 +675,8 @@ AttnSplit attn_split(const AttnArgs& a, int dv) {
     };
     constexpr float kMerge = 4.5f, kTile = 1.0f, kKeysTile = 1.8f, kKeysEdge = 1.5f;
     const int wgs = heads ? a.Hq / 4 * qb : a.Hq * ((a.T + 127) / 128);
-    AttnSplit best = cut(false, std::min(most, std::max(256 / wgs, 1)));
+    const AttnSplit plain = cut(false, std::min(most, std::max(256 / wgs, 1)));
+    AttnSplit best = plain;
     float cost = kTile * float(best.tps) + (best.runs > 1 ? kMerge : 0.0f);
     for (int r = 1; r <= most; r *= 2) {
         const AttnSplit k = cut(true, r);
@@ -675,6 +686,14 @@ AttnSplit attn_split(const AttnArgs& a, int dv) {
             cost = c;
             best = k;
         }
+    }
+    if (best.keys && plain.runs > 1) {
+        const AttnTimes& t = kAttnTimes[dv / 32 - 2];
+        const float merge = 0.7f * float(a.Hq) * float(a.T) / 1000.0f;
+        const float with_plain = t.tile * float(plain.tps) + 2.2f + merge;
+        const float with_keys = t.keys_edge + t.keys_tile * float((best.tps + 3) / 4) + t.keys_share * float(long(a.Hq) * qb * best.runs) / 256.0f +
+                                (best.runs > 1 ? 2.9f + merge : 0.0f);
+        if (with_keys >= with_plain) return plain;
     }
     return best;
 }
