@@ -391,10 +391,6 @@ __global__ __launch_bounds__(256, 1) void attn_keys_kernel(AttnArgs p, int tps) 
     const int nt_all = (kv_end + BKV - 1) / BKV;
     const int t_begin = RUNS ? int(blockIdx.z) * tps : 0, nt = RUNS ? min(nt_all, t_begin + tps) : nt_all;
     const int k_size = int(uint32_t(size_t(p.S) * p.ldk * 2)), v_size = int(uint32_t(size_t(p.dh) * p.ldv * 2));
-    const __amdgpu_buffer_rsrc_t kbuf = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(p.k + size_t(kvh) * p.k_head_stride), 0, k_size, kAttnBufferFlags);
-    const __amdgpu_buffer_rsrc_t vbuf = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(p.vt + size_t(kvh) * p.v_head_stride), 0, v_size, kAttnBufferFlags);
     // offsets, swizzles, clamps and the row of ones as in attn_kernel
     uint32_t koff[NK], voff[NV];
 #pragma unroll
@@ -409,20 +405,25 @@ __global__ __launch_bounds__(256, 1) void attn_keys_kernel(AttnArgs p, int tps) 
     }
     bf16_t *cK = sK[wave], *cV = sV[wave];
     // always as many copies, so that the waits below count the same ones everywhere: for a tile that is not there (the wavefront's
-    // last turn) they lie past the end of the buffer and fetch nothing
+    // last turn) from a buffer of no size, which fetches nothing
     auto copyK = [&](int t) {
-        const int so = t < nt ? t * (BKV * 2) * p.ldk : k_size;
+        const bool there = t < nt;
+        const __amdgpu_buffer_rsrc_t buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.k + size_t(kvh) * p.k_head_stride), 0,
+                                                                             there ? k_size : 0, kAttnBufferFlags);
 #pragma unroll
-        for (int i = 0; i < NK; ++i) DL_ATT_BLL16(kbuf, koff[i], so, cK + 512 * i);
+        for (int i = 0; i < NK; ++i) DL_ATT_BLL16(buf, koff[i], there ? t * (BKV * 2) * p.ldk : 0, cK + 512 * i);
     };
     auto copyV = [&](int t) {
-        const int so = t < nt ? t * (BKV * 2) : v_size;
+        const bool there = t < nt;
+        const __amdgpu_buffer_rsrc_t buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.vt + size_t(kvh) * p.v_head_stride), 0,
+                                                                             there ? v_size : 0, kAttnBufferFlags);
+        const int so = there ? t * (BKV * 2) : 0;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             if (ONES && i == NV - 1) {
-                if (lane < 56) DL_ATT_BLL16(vbuf, voff[i], so, cV + 512 * i);
+                if (lane < 56) DL_ATT_BLL16(buf, voff[i], so, cV + 512 * i);
             } else {
-                DL_ATT_BLL16(vbuf, voff[i], so, cV + 512 * i);
+                DL_ATT_BLL16(buf, voff[i], so, cV + 512 * i);
             }
         }
     };

@@ -805,7 +805,9 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     // showed every second LDS cycle of the kernel as a bank conflict).  Rows past the matrix edge are clamped: they produce values that the epilogue never stores.
     // Tiles in one row of tiles start at different blocks of their rows of A, tiles in one column at different blocks of B:
     // those that run on an XCD at the same time then ask its L2 for a line one after the other, and all but the first find it there.
-    // (not on 256x256: there the MFMAs hide them, and 4096^3 with an fp32 output took 1.5 us more.)
+    // (not on 256x256: there the MFMAs hide them, and 4096^3 with an fp32 output took 1.5 us more.  With / without on the other shapes,
+    // geometric means over layers of 128 .. 1536 features: K of 1024 and more 0.99, at best 0.86; K = 128 .. 768 1.008, the 0.1 us or so that the
+    // offsets take before the first copy.  A condition at run time costs short reductions the same.)
     constexpr bool ROT = BM * BN < 256 * 256;
     const int rotA = ROT ? n0 / BN * ((JA + 3) / 4) % JA : 0, rotB = ROT ? m0 / BM * ((JB + 3) / 4) % JB : 0;
     uint32_t offA[JA], offB[JB];
@@ -824,8 +826,6 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     }
     // the host only takes this path for operands below 4 GB
     const int sizeA = int(uint32_t(size_t(p.M) * p.lda * 2)), sizeB = int(uint32_t(size_t(p.N) * p.ldb * 2));
-    const __amdgpu_buffer_rsrc_t gA = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.A), 0, sizeA, kBufferFlags);
-    const __amdgpu_buffer_rsrc_t gB = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.B), 0, sizeB, kBufferFlags);
     // fragment read offsets (elements) inside a stage, one per 16-wide k step
     const int lr = lane & 31, g2 = lane >> 5;
     int rdA[4], rdB[4];
@@ -840,16 +840,18 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     const int nk = p.K / BK;                             // host guarantees K % 128 == 0: nk is even and >= 2
     // copies j0 .. j1 - 1 of a k-tile of A or B
     constexpr bool EXITS = SA != SB;
-    const int endA = sizeA < 0 ? (nk - 1) * (BK * 2) : sizeA, endB = sizeB < 0 ? (nk - 1) * (BK * 2) : sizeB;
+    // (a k-tile that is not there: a buffer of no size, which fetches nothing)
     auto copyA = [&](bf16_t* S, int kt, int j0, int j1) {
-        const int so = !EXITS || kt < nk ? kt * (BK * 2) : endA;
+        const bool there = !EXITS || kt < nk;
+        const __amdgpu_buffer_rsrc_t g = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.A), 0, there ? sizeA : 0, kBufferFlags);
 #pragma unroll
-        for (int j = j0; j < j1; ++j) DL_BLL16(gA, offA[j], so, S + blkA[j] * 512);
+        for (int j = j0; j < j1; ++j) DL_BLL16(g, offA[j], there ? kt * (BK * 2) : 0, S + blkA[j] * 512);
     };
     auto copyB = [&](bf16_t* S, int kt, int j0, int j1) {
-        const int so = !EXITS || kt < nk ? kt * (BK * 2) : endB;
+        const bool there = !EXITS || kt < nk;
+        const __amdgpu_buffer_rsrc_t g = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.B), 0, there ? sizeB : 0, kBufferFlags);
 #pragma unroll
-        for (int j = j0; j < j1; ++j) DL_BLL16(gB, offB[j], so, S + blkB[j] * 512);
+        for (int j = j0; j < j1; ++j) DL_BLL16(g, offB[j], there ? kt * (BK * 2) : 0, S + blkB[j] * 512);
     };
     auto ldfrag = [&](bf16x8* a, bf16x8* b, const bf16_t* S, const bf16_t* R, int kk) {
 #pragma unroll
@@ -937,8 +939,8 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     ldfrag(a0, b0, sa.s[0], sb.s[0], 0);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (EXITS) {
-        // every k-tile like one of the steady state, left behind the last one: its copies lie past the end of their buffer and
-        // fetch nothing (2 GB and more: fetch the last k-tile again).  Code for every remainder, as below, spilled accumulators here.
+        // every k-tile like one of the steady state, left behind the last one, whose copies fetch nothing.  Code for every
+        // remainder, as below, spilled accumulators here.
         auto turn = [&](auto self, int kt, auto i_c) -> bool {
             constexpr int I = decltype(i_c)::value;
             ktile(i_c, kt + I, integral_constant<int, SA>{});
