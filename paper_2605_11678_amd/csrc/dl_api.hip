@@ -436,6 +436,15 @@ uint64_t shared_ctx_layer_bytes(const Module& M, int32_t n_ctx) {
     return dl::align_up(2 * dkv * (uint64_t(n_ctx) + uint64_t(M.W.vtc_ld)));
 }
 
+// Where in the arena every layer's keys and values of n_ctx positions stay between the passes of one call: the decoder's activation
+// workspace, which lies idle until its next pass, if that is large enough and none of it has to stay as it is (the feed-forward's zero
+// padding).  (One position: its V^T is not the product's to write.)
+bool shared_ctx_place(const Module& act, const Module& dec, int32_t n_ctx, uint64_t* off) {
+    *off = dec.ws_off + dec.W.nbuf;
+    return n_ctx > 1 && dec.L.ffp == dec.d.d_ff && shared_ctx_layer_bytes(act, n_ctx) * uint64_t(act.d.n_layers) <=
+                                                       dec.W.mid + 2ull * uint64_t(dec.d.max_tokens) * uint64_t(dec.d.d_ff) - dec.W.nbuf;
+}
+
 void run_layer(dl_ctx* c, Module& M, int32_t layer, const uint8_t* w, const float* in, float* out, int32_t T,
                int32_t pos0, const float* ctx, int32_t n_ctx, const SharedCtx& sc = SharedCtx()) {
     const dl_module_desc& d = M.d;
@@ -1295,20 +1304,18 @@ int32_t dl_vla_infer(dl_ctx* c, const dl_vla_desc* v, const dl_vla_buffers* b) {
     }
     // stage 5: Euler steps of the action stack against the fixed context, then the trajectory head.  A step's update and the next
     // step's time embedding are one launch.  The first step converts the context to bf16 and makes the cross-attention's keys and values
-    // of every layer; the others find them in the decoder's activation workspace, which lies idle until its next pass, if that is large
-    // enough and none of it has to stay as it is (the feed-forward's zero padding).  Ten steps of two 256-wide layers over 160
-    // positions: 18 of 20 products of ~5.5 us; of eight 1024-wide layers over 3072 positions: 72 of 80 products of 47 us.
+    // of every layer; the others find them in the decoder's activation workspace, if they may stay there (shared_ctx_place).  Ten steps of
+    // two 256-wide layers over 160 positions: 18 of 20 products of ~5.5 us; of eight 1024-wide layers over 3072 positions: 72 of 80
+    // products of 47 us.
     SharedCtx sc;
-    const uint64_t kv_layer = shared_ctx_layer_bytes(*act, n_prefill), kv_bytes = kv_layer * uint64_t(act->d.n_layers);
-    const bool share = on_gpu(c) && v->n_euler > 1 && n_prefill > 1 && dec->L.ffp == dec->d.d_ff &&
-                       kv_bytes <= dec->W.mid + 2ull * uint64_t(dec->d.max_tokens) * uint64_t(dec->d.d_ff) - dec->W.nbuf;
-    if (share) {
-        sc.kv = c->base + dec->ws_off + dec->W.nbuf;
+    uint64_t kv_off = 0;
+    if (on_gpu(c) && v->n_euler > 1 && shared_ctx_place(*act, *dec, n_prefill, &kv_off)) {
+        sc.kv = c->base + kv_off;
         // attention reads whole tiles of 64 positions and wants finite numbers there
         if (n_prefill % 64) {
             const int dkv = act->d.n_kv_heads * act->d.d_head;
-            dlk::zero_positions(reinterpret_cast<bf16_t*>(sc.kv) + uint64_t(n_prefill) * dkv, kv_layer / 2, act->d.n_layers, dkv, act->W.vtc_ld,
-                                n_prefill, n_prefill / 64 * 64 + 64, c->s_compute);
+            dlk::zero_positions(reinterpret_cast<bf16_t*>(sc.kv) + uint64_t(n_prefill) * dkv, shared_ctx_layer_bytes(*act, n_prefill) / 2,
+                                act->d.n_layers, dkv, act->W.vtc_ld, n_prefill, n_prefill / 64 * 64 + 64, c->s_compute);
         }
     }
     const float dt = 1.0f / float(v->n_euler);
@@ -1832,3 +1839,13 @@ int32_t dl_trace_read(dl_ctx* c, dl_trace_op* out, int32_t cap, int32_t* n_out) 
 }
 
 }  // extern "C"
+
+// For tests (host only): whether dl_vla_infer keeps the action stack's keys and values of n_ctx positions between its Euler steps, and where:
+// arena offset, bytes of a layer.
+extern "C" __attribute__((visibility("default"))) int32_t dlk_shared_ctx(dl_ctx* c, int32_t m_act, int32_t m_dec, int32_t n_ctx, uint64_t* off,
+                                                                         uint64_t* layer_bytes) {
+    const Module *act = get_module(c, m_act), *dec = get_module(c, m_dec);
+    if (!act || !dec) return -1;
+    *layer_bytes = shared_ctx_layer_bytes(*act, n_ctx);
+    return shared_ctx_place(*act, *dec, n_ctx, off) ? 1 : 0;
+}
