@@ -100,8 +100,8 @@ void norm_rows(int kind, const float* x, const bf16_t* g, const bf16_t* b, void*
 void cast_f32_bf16(const float* x, bf16_t* out, uint64_t n, hipStream_t st);
 
 // ---- attention (flash-style, online softmax, MFMA) ------------------------------------------------
-// The V^T rows must be readable up to S rounded up to 8 positions and hold finite numbers there (stale values are
-// fine: they meet zero probabilities); K rows and V^T rows are read in 16-byte pieces (ldk, ldv multiples of 8).
+// The V^T rows must be readable up to S rounded up to 64 positions and hold finite numbers there (whole tiles are read; stale values
+// are fine: they meet zero probabilities); K rows and V^T rows are read in 16-byte pieces (ldk, ldv multiples of 8).
 inline float attention_q_scale(int dh) { return 1.4426950408889634f / sqrtf(float(dh)); }
 struct AttnArgs {
     const bf16_t* q; int ldq;                         // token t, head h: q + t*ldq + h*dh, times attention_q_scale(dh)
@@ -134,9 +134,9 @@ void decode_attention(const DecodeAttnArgs& a, hipStream_t st);
 // ---- small elementwise helpers of the multi-module pipeline (fp32 activations) ----------------------
 // y[t, :] = mean over j < group of x[t*group + j, :]
 void mean_pool_rows(const float* x, float* y, int T_out, int group, int d, hipStream_t st);
-// y[i] += alpha * x[i]
-// positions [from, to) of `layers` x `rows` V^T rows of ld elements become zero (layers are layer_stride elements apart)
+// positions [from, to) of `layers` x `rows` V^T rows of ld elements become zero (layers are layer_stride elements apart); at most 64 of them
 void zero_positions(bf16_t* vt, uint64_t layer_stride, int layers, int rows, int ld, int from, int to, hipStream_t st);
+// y[i] += alpha * x[i]
 void axpy_f32(float* y, float alpha, const float* x, uint64_t n, hipStream_t st);
 // y[t, i] = x[t, i] + (i < d/2 ? sin : cos)(1000 * tval * 10000^(-(i mod d/2) / (d/2)))
 void add_time_embedding(const float* x, float* y, float tval, int T, int d, hipStream_t st);

@@ -20,7 +20,7 @@
 //    128x128).  They come in at about 60 bytes per ns and compute unit where lines miss the L2, at twice that where they hit
 //    (every k-tile among the first eight: 128x128 148 -> 121 us); tiles that share lines ask for them at the same time.
 //  * gemm_generic<EPI> — any shape (K % 8 == 0): 128x128 tile, 64x64 per wavefront, staged through registers.
-//  * gemm_few_rows<BM,BN,NS,EPI> — M <= 64: BN output columns per workgroup, reduction split over its 4 wavefronts.
+//  * gemm_few_rows<BM,BN,NS,EPI,NORM> — M <= 64: BN output columns per workgroup, reduction split over its 4 wavefronts.
 //
 // Accumulator layout of a 32x32 tile: lane l, register r -> column l%32, row 8*(r/4) + 4*(l/32) + r%4.
 #include <type_traits>

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256) void mean_pool_kernel(const float* __restrict_
 
 __global__ __launch_bounds__(256) void zero_positions_kernel(bf16_t* vt, uint64_t layer_stride, int rows, int ld, int from, int to) {
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int pos = from + (threadIdx.x & 63);             // at most 63 positions
+    const int pos = from + (threadIdx.x & 63);             // at most 64 positions
     if (row < rows && pos < to) vt[uint64_t(blockIdx.y) * layer_stride + uint64_t(row) * uint64_t(ld) + uint64_t(pos)] = 0;
 }
 
