@@ -46,7 +46,8 @@ hipError_t static_scratch_ptr(int32_t device, void** out) {
 
 // Logits up to here (64 KB) come to the host by the kernel that looks for the largest, into pinned memory, and the host copies them on:
 // head, choice and logits of 1024 / 4096 / 16384 take 21.9 / 23.2 / 28.6 us that way, 32.6 / 33.6 / 39.9 with a copy into the caller's
-// pageable memory behind the launch.  More of them keep that copy (32768: 45.7 us): a module does not pin more than this for it.
+// pageable memory behind the launch.  More of them keep that copy (32768: 45.7 us); the limit is the largest size measured, not where the
+// gain ends.
 constexpr int32_t kPinnedLogits = 16384;
 uint64_t head_host_bytes(const dl_module_desc& d) {
     return d.vocab <= 0 ? 0 : 256 + (d.vocab <= kPinnedLogits ? 4 * uint64_t(d.vocab) : 0);

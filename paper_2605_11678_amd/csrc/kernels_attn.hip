@@ -681,7 +681,7 @@ AttnSplit attn_split(const AttnArgs& a, int dv) {
     float cost = kTile * float(best.tps) + (best.runs > 1 ? kMerge : 0.0f);
     for (int r = 1; r <= most; r *= 2) {
         const AttnSplit k = cut(true, r);
-        if (long(a.Hq) * qb * k.runs > 256) break;         // one workgroup to a compute unit: no second round
+        if (long(a.Hq) * qb * k.runs > 256) break;         // a second round loses more (731 patches, 800 tokens) than it wins (500)
         const float c = kKeysEdge + kKeysTile * float((k.tps + 3) / 4) + (k.runs > 1 ? kMerge : 0.0f);
         if (c < cost) {
             cost = c;

@@ -880,12 +880,13 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     // and meets the others at the one barrier of the k-tile; past it (a) k-tile kt+1 has landed for everyone and
     // (b) nobody reads the stages of kt any more, so the copies into them start right there: B of kt+SB in the last phase and the
     // first of the next k-tile, A of kt+SA in the two that follow.  Four phases with a quarter of the copies each: a wavefront
-    // that issues more at a time waits in front of the copy path, and its MFMAs with it (256 x 128 wavefront pairs, 128x256 on three:
-    // 4096^3 116.5 -> 111.6 us, 4096 x 1152, K = 4352: 48.0 -> 44.8).  On two stages there is no time for that, a copy has to land
-    // within a k-tile: A goes with the last phase, B with the first (the other way round, 256x256 with 4096^3 and an fp32 output took
-    // 2 us more).
+    // that issues more at a time waits in front of the copy path, and its MFMAs with it (128x256 on three, 517 x 24576, K = 4096:
+    // 111.1 -> 106.8 us; the 25 of 810 problems that take this shape 4 % faster, the shapes of at most 192x192 0 to 2.5 %).  On two stages
+    // there is no time for that, a copy has to land within a k-tile: A goes with the last phase, B with the first (the other way round,
+    // 256x256 with 4096^3 and an fp32 output took 2 us more, the one product that this was measured on).
     // 192x256 and 256x192 have two stages of the operand with more to copy and four or three of the other: half of the copies get a
-    // k-tile or two more to land (192x256: 3072 x 4096, K = 12288, 238 -> 220 us; 3072 x 6144, K = 4096, 156 -> 137).
+    // k-tile or two more to land (192x256, 3072 x 4096: K = 12288 250.8 -> 234.2 us, K = 4096 91.8 -> 88.2; the 48 problems that take one of
+    // the two 9 % faster).
     // REM = k-tiles after this one, capped at SA (the steady state): with too few left a copy has nothing to fetch; the wait
     // leaves the copies younger than k-tile kt+1 in flight.
     constexpr bool SPREAD = SA > 2;
