@@ -1070,11 +1070,11 @@ void launch_fast(const GemmArgs& a, hipStream_t st) {
 // the shapes that come near the fastest; an added constant for the launch (1.8) is left out, being the same for all.  (Inside a
 // layer, at the clock that a whole pass settles at, the same launches take up to a fifth longer.)  Median error 7 %; the shape
 // taken is 0.5 % (geometric mean) slower than the fastest, 1.7 % of the problems lose more than 10 %.  Fitted without 342 of
-// the problems, the choice loses 0.9 % on these.  (Since the copies are spread and rotated every shape but 256x256 is 1 to 8 % faster,
-// 192x256 and 256x192 most; on the times measured then, which the test holds, the same table loses 0.6 % and 1.6 % of the problems more than
-// 10 %, a new fit of these two rows 0.55 %.)  (A table fitted to M up to 4096 without a column for the residual,
-// with one entry set by hand, and blind to the split tail, lost 3.0 % on all and 3.4 % on these: 4096 x 1152 residual outputs, K =
-// 1152, 23.4 us where 128x128 tiles take 20.0; K = 4352, 51.6 where 192x128 take 46.4.)
+// the problems, the choice loses 0.9 % on these.  (On the times of the kernels as they are now, which the test holds, the same
+// table loses 0.8 %, and 2.5 % of the problems more than 10 %: the copies that were spread since made 192x256 and 256x192 8 % faster,
+// 128x256 4 %, the others by up to 1 %.)  (A table fitted to M up to 4096 without a column for the residual, with one entry set by
+// hand, and blind to the split tail, lost 3.0 % on all and 3.4 % on these: 4096 x 1152 residual outputs, K = 1152, 23.4 us where
+// 128x128 tiles take 20.0; K = 4352, 51.6 where 192x128 take 46.4.)
 // What separates the shapes: a compute unit takes in about 40 bytes per clock through the global -> LDS path whatever the tile,
 // so large tiles need fewer bytes per flop and win as soon as there are rounds of them; and a copy takes up to ~1.3 us to
 // land (weights cold), more than a small tile's k-tile lasts, so tiles of at most 128x160 run on four to eight stages

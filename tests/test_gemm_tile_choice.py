@@ -1,5 +1,5 @@
-"""The tile shape that the GEMM dispatcher takes, against the measured times of every shape (MI355X, us per launch, launches in a row with
-cold weights) on 810 problems (rows, columns, reduction, epilogue).  Host only: the times are stored, the choice is the library's."""
+"""The tile shape that the GEMM dispatcher takes, against the measured times of every shape (MI355X, us per launch, launches in a row,
+weights from up to 40 places in turn, the smaller of two runs' medians) on 810 problems (rows, columns, reduction, epilogue).  Host only: the times are stored, the choice is the library's."""
 import os
 
 import numpy as np
@@ -16,7 +16,7 @@ def test_choice_against_measured_times():
     taken = np.array([us[i, tiles.index(tile_of(*p))] for i, p in enumerate(z["problems"])])
     assert np.all(np.isfinite(taken))                    # a shape that the problem allows
     loss = taken / us.min(1)
-    # 0.5 % geometric mean and 1.29 at most as fitted (two runs of the same problems put the best shape within 0.1 % and 1.06)
+    # 0.8 % geometric mean, 1.31 at most, 2.5 % above 1.1 (on the times that the rule was fitted to: 0.5 %, 1.29, 1.7 %)
     assert np.exp(np.mean(np.log(loss))) <= 1.01 and loss.max() <= 1.35 and np.mean(loss > 1.1) <= 0.03
     # and over each epilogue alone
     for e in range(5):
