@@ -806,23 +806,24 @@ __device__ __forceinline__ void fast_tile_any(const GemmArgs& p, int m0, int n0,
     // Tiles in one row of tiles start at different blocks of their rows of A, tiles in one column at different blocks of B:
     // those that run on an XCD at the same time then ask its L2 for a line one after the other, and all but the first find it there.
     // (not on 256x256: there the MFMAs hide them, and 4096^3 with an fp32 output took 1.5 us more.  With / without on the other shapes,
-    // geometric means over layers of 128 .. 1536 features: K of 1024 and more 0.99, at best 0.86; K = 128 .. 768 1.008, the 0.1 us or so that the
-    // offsets take before the first copy.  A condition at run time costs short reductions the same.)
+    // geometric means over layers of 128 .. 1536 features: K of 1024 and more 0.99, at best 0.86; at K = 128 and 256 up to 0.05 us more, what the
+    // offsets take before the first copy: 768 columns, K = 256, 6.24 -> 6.29 us on average, 6.34 with the chunk of every block computed anew.
+    // A condition at run time costs short reductions the same.)
     constexpr bool ROT = BM * BN < 256 * 256;
     const int rotA = ROT ? n0 / BN * ((JA + 3) / 4) % JA : 0, rotB = ROT ? m0 / BM * ((JB + 3) / 4) % JB : 0;
+    // a wavefront's blocks are four apart, so (row/2)%8 of a lane's row is the same in all of them
+    const int lc = (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7);
     uint32_t offA[JA], offB[JB];
     int blkA[JA], blkB[JB];
 #pragma unroll
     for (int j = 0; j < JA; ++j) {
         blkA[j] = wave + 4 * (j + rotA < JA ? j + rotA : j + rotA - JA);
-        const int row = 8 * blkA[j] + (lane >> 3), lc = (lane & 7) ^ ((row >> 1) & 7);
-        offA[j] = uint32_t((size_t(min(m0 + row, p.M - 1)) * p.lda + lc * 8) * 2);
+        offA[j] = uint32_t((size_t(min(m0 + 8 * blkA[j] + (lane >> 3), p.M - 1)) * p.lda + lc * 8) * 2);
     }
 #pragma unroll
     for (int j = 0; j < JB; ++j) {
         blkB[j] = wave + 4 * (j + rotB < JB ? j + rotB : j + rotB - JB);
-        const int row = 8 * blkB[j] + (lane >> 3), lc = (lane & 7) ^ ((row >> 1) & 7);
-        offB[j] = uint32_t((size_t(min(n0 + row, p.N - 1)) * p.ldb + lc * 8) * 2);
+        offB[j] = uint32_t((size_t(min(n0 + 8 * blkB[j] + (lane >> 3), p.N - 1)) * p.ldb + lc * 8) * 2);
     }
     // the host only takes this path for operands below 4 GB
     const int sizeA = int(uint32_t(size_t(p.M) * p.lda * 2)), sizeB = int(uint32_t(size_t(p.N) * p.ldb * 2));
