@@ -1072,7 +1072,7 @@ void launch_fast(const GemmArgs& a, hipStream_t st) {
 // layer, at the clock that a whole pass settles at, the same launches take up to a fifth longer.)  Median error 7 %; the shape
 // taken is 0.5 % (geometric mean) slower than the fastest, 1.7 % of the problems lose more than 10 %.  Fitted without 342 of
 // the problems, the choice loses 0.9 % on these.  (On the times of the kernels as they are now, which the test holds, the same
-// table loses 0.8 %, and 2.5 % of the problems more than 10 %: the copies that were spread since made 192x256 and 256x192 8 % faster,
+// table loses 0.8 %, and 2.0 % of the problems more than 10 %: the copies that were spread since made 192x256 and 256x192 8 % faster,
 // 128x256 4 %, the others by up to 1 %.)  (A table fitted to M up to 4096 without a column for the residual, with one entry set by
 // hand, and blind to the split tail, lost 3.0 % on all and 3.4 % on these: 4096 x 1152 residual outputs, K = 1152, 23.4 us where
 // 128x128 tiles take 20.0; K = 4352, 51.6 where 192x128 take 46.4.)
